@@ -1,0 +1,39 @@
+// Which kernel a product takes, as functions of its sizes alone (host code without HIP, so that tests can compile it
+// and check that the sizes they run still take the route they are meant for).
+#pragma once
+
+namespace san {
+
+// fp32 through the bf16 matrix cores (gemm_split.hip): tile height (64 wm rows; 0: the fp32 instructions are faster)
+// and k split in [ks_min, ks_max].  A model of both routes, in us:
+//   split   3 + 21 (128 rows) or 30 (192) for k = 512 and every round of one block per CU, in proportion to k, and
+//           what the consumer pays for further partials (written and read at 4 TB/s)
+//   plain   4 + 2 M N K flops at 95 TFLOP/s, M in whole tiles of 64
+// Where the column tiles are no multiple of eight the row tiles of one column tile stay on one XCD, so a round is 32
+// blocks of the XCD that has most of them (plain: the 128 x 128 tiles, which products of 200 such tiles take).
+// Measured (us, split / plain): outputs of 65, 185, 256 and 512 rows x 32000 at k = 512 24.7 / 37.0, 34.7 / 66.7,
+// 46.6 / 67.4, 87.9 / 130, 128 x 32000 x 256 16.6 / 21.5, x 1024 44.0 / 65.1; 3840 x 2048 x 512 47.3 / 67.3,
+// 2257 x 1536 x 512 33.1 / 66.1, 1000 x 4096 x 1024 44.8 / 65.6, 3840 x 512 x 2048 (k in two) 44.3 / 69.9,
+// 2048 x 1024 x 4096 (two) 81.7 / 133; left to the plain kernel 256 x 8000 x 512 23.3 / 22.2, 3840 x 512 x 512
+// 25.2 / 22.9, 512 x 1024 x 1024 14.8 / 13.1.  Over 361 shapes of 64 to 7680 rows, k 256 to 4096, the choice lost
+// 4 % or more on one.
+struct SplitShape { int wm, ks; };
+inline SplitShape gemm_split_shape(int M, int N, int K, int ks_min, int ks_max) {
+  SplitShape best{0, 1};
+  if (K % 64 || M < 1 || N < 1) return best;
+  const long cols = ((long)N + 127) / 128, rows128 = ((long)M + 127) / 128;
+  const bool by_xcd = cols % 8 != 0;
+  const float uneven = by_xcd && M > 128 && rows128 * cols >= 200 ? (float)((cols + 7) / 8 * 8) / (float)cols : 1.f;
+  float best_us = 0.85f * (4.f + uneven * 2.f * ((M + 63) / 64 * 64) * (float)N * (float)K / 95e6f);
+  for (int wm = 2; wm <= 3; ++wm)
+    for (int ks = ks_min; ks <= ks_max; ks *= 2) {
+      if (K % (64 * ks) || (ks > 1 && K / ks < 512)) continue;
+      const long rows = ((long)M + 64 * wm - 1) / (64 * wm);
+      const long rounds = by_xcd && rows > 1 && ks == 1 ? ((cols + 7) / 8 * rows + 31) / 32 : (cols * rows * ks + 255) / 256;
+      const float us = 3.f + (float)rounds * (wm == 2 ? 21.f : 30.f) * (float)K / (512.f * ks) + 2e-6f * (ks - 1) * (float)M * (float)N;
+      if (us < best_us) { best_us = us; best = SplitShape{wm, ks}; }
+    }
+  return best;
+}
+
+}  // namespace san

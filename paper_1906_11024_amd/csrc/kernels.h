@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_rules.h"
+
 namespace san {
 
 // ---------------------------------------------------------------- projections
@@ -49,10 +51,8 @@ int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain);
 int gemm_cand_tile_n(int M, int N, int K, int dtype);
 
 // fp32 only: the same product through the bf16 matrix cores with every operand split into three bf16 parts
-// (gemm_split.hip).  gemm_split_shape: the tile height (64 * wm rows) and k split that route would take, wm = 0 where
-// it is not the faster one.  launch_gemm takes it by itself unless `plain` is set.
-struct SplitShape { int wm, ks; };
-SplitShape gemm_split_shape(int M, int N, int K, int ks_min, int ks_max);   // k split in [ks_min, ks_max]
+// (gemm_split.hip), tiles of 64 * wm rows.  launch_gemm takes it by itself where gemm_split_shape says so, unless
+// `plain` is set.
 hipError_t launch_gemm_split(const GemmParams& p, int wm, hipStream_t stream);
 // *flag = 1 if one of the n fp32 values is not finite or rounds to infinity in bf16 (gemm_split.hip cannot take it)
 hipError_t launch_check_splittable(const float* w, size_t n, int* flag, hipStream_t stream);

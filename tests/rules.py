@@ -1,0 +1,27 @@
+"""The library's route rules (csrc/gemm_rules.h, host code without HIP), compiled for the tests: a test that is meant
+for one route asserts with them that its sizes still take it."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+_HERE = os.path.dirname(os.path.abspath(__file__))
+_WRAPPER = """
+#include "gemm_rules.h"
+extern "C" int split_wm(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).wm; }
+extern "C" int split_ks(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).ks; }
+"""
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as tmp:
+            src, so = os.path.join(tmp, "rules.cpp"), os.path.join(tmp, "librules.so")
+            with open(src, "w") as fh:
+                fh.write(_WRAPPER)
+            subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I",
+                            os.path.join(_HERE, "..", "paper_1906_11024_amd", "csrc"), src, "-o", so], check=True)
+            _lib = C.CDLL(so)
+    return _lib

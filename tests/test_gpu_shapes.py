@@ -10,6 +10,7 @@ torch = pytest.importorskip("torch")
 
 from paper_1906_11024_amd import workloads as wl
 from tests import harness as hz
+from tests import rules
 from tests.test_gpu_parity import BF16_TOL, F32_TOL
 
 
@@ -69,16 +70,71 @@ def test_few_rows_match_oracle(case, loop):
     ls.gpu.close()
 
 
-# a wide vocabulary whose last column tile has 4 live columns, k = 192 (an odd number of chunk pairs) and 256.
-# 100 / 128 rows take tiles of 128, 185 of 192, 256 of 256, 300 two of 192.  debug = 2: the fp32 instructions instead.
+# a wide vocabulary whose last column tile has 4 live columns, k = 192 (an odd number of chunk pairs) and 256; wm: tiles
+# of 64 wm rows (100 rows of 128, 185 of 192, 256 two full tiles of 128, 300 two of 192, the second ragged).
+# debug = 2: the fp32 instructions instead.
 @pytest.mark.parametrize("loop", [None, "cands"])
-@pytest.mark.parametrize("batch,beam,d,debug", [(25, 4, 192, 0), (32, 4, 256, 0), (37, 5, 192, 0), (64, 4, 192, 0),
-                                                (300, 1, 192, 0), (64, 4, 192, 2)])
-def test_large_fp32_products_match_oracle(batch, beam, d, debug, loop):
+@pytest.mark.parametrize("batch,beam,d,debug,wm", [(25, 4, 192, 0, 2), (32, 4, 256, 0, 2), (37, 5, 192, 0, 3), (64, 4, 192, 0, 2),
+                                                   (300, 1, 192, 0, 3), (64, 4, 192, 2, 2)])
+def test_large_fp32_products_match_oracle(batch, beam, d, debug, wm, loop):
+    assert rules.lib().split_wm(batch * beam, 25604, d, 1, 1) == wm
     ls = _lockstep(_cfg(batch=batch, beam=beam, d=d, H=d // 64, V=25604, steps=2, n_dec=1, self_pi=[1], encdec_pi=[1]), loop=loop, debug=debug)
     if loop is None:
         assert max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
     ls.gpu.close()
+
+
+def _logits_of(cfg, row, w_out, debug):
+    """Logits of a one-step decode whose decoder output is `row` for every hypothesis: the last LayerNorm has gain 0
+    and bias `row`."""
+    w = wl.make_weights(cfg, seed=4)
+    w["dec0.ln3.g"] = np.zeros_like(w["dec0.ln3.g"])
+    w["dec0.ln3.b"] = row
+    w["w_out"] = w_out
+    src, lens = wl.make_source(cfg, 4)
+    gpu = hz.make_gpu(cfg, w, debug=debug)
+    logits = torch.empty((cfg["batch"], cfg["V"]), dtype=torch.float32, device="cuda")
+    gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+    gpu.decode_step(torch.full((cfg["batch"],), wl.BOS_ID, dtype=torch.int32, device="cuda"), logits)
+    out = logits.cpu().numpy()
+    gpu.close()
+    return out
+
+
+@pytest.mark.parametrize("batch", [128, 185])
+@pytest.mark.parametrize("operands", ["normal", "spread", "relu", "one_live", "below_half_step", "signed_half_step"])
+def test_split_products_are_no_further_from_64_bits(operands, batch):
+    """fp32 products through bf16 parts against the fp32 instructions (debug = 2), both against 64 bits: rows of random
+    values, of values spread over e^+-8, of non-negative ones (a ReLU's output), a single live value, and operands whose
+    bf16 parts are as large as they get, with one sign and with random ones."""
+    V, d = 32000, 512
+    assert rules.lib().split_wm(batch, V, d, 1, 1) == (2 if batch == 128 else 3)
+    rng = np.random.default_rng(11)
+    row, w_out = rng.normal(size=d), 0.02 * rng.normal(size=(V, d))
+    step = np.nextafter(np.float32(1.00390625), np.float32(0))          # 1 + 2^-8, less one unit of the 24th bit
+    if operands == "spread":
+        row, w_out = row * np.exp(rng.uniform(-8, 8, d)), w_out * np.exp(rng.uniform(-8, 8, (V, d)))
+    elif operands == "relu":
+        row = np.maximum(row, 0)
+    elif operands == "one_live":
+        row[np.arange(d) != 77] = 0
+    elif operands == "below_half_step":
+        row, w_out = np.full(d, step), np.full((V, d), step)
+    elif operands == "signed_half_step":
+        row, w_out = step * np.sign(row), step * np.sign(w_out)
+    row, w_out = row.astype(np.float32), w_out.astype(np.float32)
+    cfg = _cfg(batch=batch, d=d, H=8, F=64, V=V, n_dec=1, self_pi=[1], encdec_pi=[1])
+    exact = w_out.astype(np.float64) @ row.astype(np.float64)
+    err = []
+    for debug in (0, 2):
+        got = _logits_of(cfg, row, w_out, debug)
+        assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+        err.append(np.linalg.norm(got[0] - exact) / np.linalg.norm(exact))
+    # 1 % for the two roundings of the last addition, where that is all there is
+    assert err[0] <= 1.01 * err[1], err
+    # one rounding of the running sum per 16 products, one for joining the two sums: sqrt(d / 16 + 1) of them at 2^-25
+    # rms each add up like this when they are independent; 4 times that covers sums that are larger than the result
+    assert err[0] <= 4 * np.sqrt(d / 16 + 1) * 2.0 ** -25, err
 
 
 def test_infinite_weight_keeps_its_logits():
