@@ -54,7 +54,7 @@ int gemm_cand_tile_n(int M, int N, int K, int dtype);
 // (gemm_split.hip), tiles of 64 * wm rows.  launch_gemm takes it by itself where gemm_split_shape says so, unless
 // `plain` is set.
 hipError_t launch_gemm_split(const GemmParams& p, int wm, hipStream_t stream);
-// *flag = 1 if one of the n fp32 values is not finite or rounds to infinity in bf16 (gemm_split.hip cannot take it)
+// *flag = 1 if one of the n fp32 parameters is 2^16 or larger, or not finite (gemm_split.hip cannot take the model)
 hipError_t launch_check_splittable(const float* w, size_t n, int* flag, hipStream_t stream);
 
 // A second update + LayerNorm applied to a first one's output in the same launch:

@@ -105,7 +105,7 @@ struct san_ctx {
   std::vector<DecLayer> dec;
   void *src_emb = nullptr, *tgt_emb = nullptr, *w_out = nullptr;
   float* pe = nullptr;
-  bool plain = false;          // fp32 products by the fp32 instructions only (weights gemm_split.hip cannot take, or cfg.debug & 2)
+  bool plain = false;          // fp32 products by the fp32 instructions only (parameters gemm_split.hip cannot take, or cfg.debug & 2)
   std::vector<std::pair<void*, size_t>> weights;   // every weight allocation and its bytes
   // workspaces
   void *x = nullptr, *qkv = nullptr, *ab = nullptr, *hb = nullptr, *cat = nullptr;
@@ -586,9 +586,8 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
     HIP_TRY(c, hipMemset(c->t_dev, 0, 256));
     if (c->dt == SAN_F32) {
       c->plain = (cfg->debug & 2) != 0;
-      for (const auto& w : c->weights)
-        if (w.second >= 64 * 64 * 4)   // the matrices (64 x 64 at least); biases and gains are not split
-          HIP_TRY(c, launch_check_splittable((const float*)w.first, w.second / 4, c->t_dev, nullptr));
+      // every parameter: gains and biases are not split themselves, but what they make of the activations is
+      for (const auto& w : c->weights) HIP_TRY(c, launch_check_splittable((const float*)w.first, w.second / 4, c->t_dev, nullptr));
       int flag = 0;
       HIP_TRY(c, hipMemcpy(&flag, c->t_dev, 4, hipMemcpyDeviceToHost));
       if (flag) c->plain = true;

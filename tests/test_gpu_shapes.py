@@ -161,6 +161,23 @@ def test_infinite_weight_keeps_its_logits():
     assert np.allclose(rows[0][:, others], rows[1][:, others], rtol=0, atol=1e-4 * np.abs(rows[0][:, others]).max())
 
 
+@pytest.mark.parametrize("value", [np.inf, -np.inf, 3.4e38, 1e6])
+def test_activations_too_large_to_split(value):
+    """A bias of the last LayerNorm that is infinite, rounds to infinity in bf16 or is merely large: the logits are what
+    the fp32 instructions give, infinite with the weight's sign or finite."""
+    cfg = _cfg(batch=256, d=192, H=3, V=25604, n_dec=1, self_pi=[1], encdec_pi=[1])
+    assert rules.lib().split_wm(256, 25604, 192, 1, 1) > 0
+    rng = np.random.default_rng(6)
+    row, w_out = rng.normal(size=192).astype(np.float32), (1e-3 * rng.normal(size=(25604, 192))).astype(np.float32)
+    row[5] = value
+    got = _logits_of(cfg, row, w_out, 0)
+    if np.isinf(value):
+        assert np.array_equal(got, np.broadcast_to(np.sign(value) * np.sign(w_out[:, 5]) * np.float32(np.inf), got.shape))
+    else:
+        assert np.isfinite(got).all()
+    assert np.array_equal(got, _logits_of(cfg, row, w_out, 2))
+
+
 @pytest.mark.parametrize("dtype,batch,max_src,share,enc_pi", [("f32", 40, 61, "A", None), ("bf16", 33, 70, "S", None),
                                                               ("f32", 20, 30, "A", [2, 1]), ("f32", 1030, 5, "A", None)])
 def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_pi):
