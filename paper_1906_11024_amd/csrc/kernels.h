@@ -5,7 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "gemm_rules.h"
+#include "rules.h"
 
 namespace san {
 

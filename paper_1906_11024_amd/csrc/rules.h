@@ -1,5 +1,5 @@
-// Which kernel a product takes, as functions of its sizes alone (host code without HIP, so that tests can compile it
-// and check that the sizes they run still take the route they are meant for).
+// Which route a call takes, as functions of its sizes alone (host code without HIP, so that tests can compile it and
+// check that the sizes they run still take the route they are meant for).
 #pragma once
 
 namespace san {

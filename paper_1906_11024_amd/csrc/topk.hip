@@ -118,8 +118,8 @@ __device__ __forceinline__ void merge_mirrored(Cand& c, float ov, int oi, int la
 // The k best (k <= 32) of `lists` <= 32 lists of k candidates load(list, position), by a block of four waves; lanes
 // 0..k-1 of wave 0 end up with them, best first (s_v, s_i: LDS, 128 entries).  All candidates are requested at once,
 // each half-wave sorts its up to four lists (15 stages) and merges them (6 each), then the halves and the waves meet:
-// at most 85 stages one after the other, where one wave sorting 64 candidates per pass needs 42 for every 64
-// (400 candidates: 294).  Beam tail of 24 sentences, beam 20: 44 -> 15 us, half of it the sentence's state and embedding.
+// 15 + 6 stages per list after the first, 18 more for the meeting: 75 for 20 lists, 96 for 32, where one wave sorting 64
+// candidates per pass needs 42 for every 64 (400 candidates: 294).  Beam tail of 24 sentences, beam 20: 44 -> 15 us, half of it the sentence's state and embedding.
 template <typename F> __device__ __forceinline__ Cand block_topk(F load, int lists, int k, int tid, float* s_v, int* s_i) {
   const int lane = tid & 63, wid = tid >> 6, half = lane >> 5, pos = lane & 31;
   Cand l[4];
@@ -225,20 +225,30 @@ __global__ __launch_bounds__(kTopkThreads) void topk_row_kernel(const float* log
     // >= T, and usually only a handful of elements are.  Those go to a short list in
     // LDS that wave 0 orders; a list overflow (masses of equal values) falls back to
     // the general rounds below.  T = the k-th largest wave maximum (k <= 16 waves;
-    // already known from the log-sum-exp), else the k-th largest of the 32 half-wave
-    // maxima: about 31 elements pass for k = 20 (each wave's k largest thread maxima,
-    // sorted and merged, let fewer pass, but cost 200 sorting stages: 480 rows of
-    // 32000, k = 20, 40 us; now 20).
+    // already known from the log-sum-exp), else the k-th largest of the maxima of 32 groups:
+    // lanes l and l + 32 of every wave, words 4 l .. 4 l + 3 of every 128.  Every group has
+    // words from 128 words on, and words ordered by their score spread over the groups.  About
+    // 31 elements pass for k = 20 and 130 for k = 32; each wave's k largest thread maxima, sorted
+    // and merged, let fewer pass, but cost 200 sorting stages, and the maxima of 128 neighbouring
+    // words are too few over small vocabularies.  san_topk of 24 sentences, beam 20 (us, thread
+    // maxima / neighbouring words / now): 1000 words 50 / 52 / 22, 2004 50 / 136 / 22, 32000
+    // 54 / 27 / 27, 32000 in order of their scores 56 / 191 / 29.
     const bool by_wave_max = k <= NW;
     if (!by_wave_max) {
-      const float m_h = max_xor16(group_max<16>(tmax));
-      if ((lane & 31) == 0) wc_v[wid * 2 + (lane >> 5)] = m_h;
+      const float m_g = max_xor32(tmax);
+      if (lane < 32) wc_v[wid * 32 + lane] = m_g;
     }
     if (tid == 0) list_n = 0;
     __syncthreads();
     if (wid == 0) {
+      float m_g = -INFINITY;
+      if (!by_wave_max) {
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) m_g = fmaxf(m_g, wc_v[((lane >> 5) * (NW / 2) + w) * 32 + (lane & 31)]);
+        m_g = max_xor32(m_g);
+      }
       const Cand c = by_wave_max ? wave_topk([&](int q) { return Cand{red_m[q], q}; }, NW, k, lane)
-                                 : wave_topk([&](int q) { return Cand{wc_v[q], q}; }, NW * 2, k, lane);
+                                 : wave_topk([&](int q) { return Cand{m_g, q}; }, 32, k, lane);
       if (lane == k - 1) thresh = c.v;
     }
     __syncthreads();

@@ -1,4 +1,4 @@
-"""The library's route rules (csrc/gemm_rules.h, host code without HIP), compiled for the tests: a test that is meant
+"""The library's route rules (csrc/rules.h, host code without HIP), compiled for the tests: a test that is meant
 for one route asserts with them that its sizes still take it."""
 import ctypes as C
 import os
@@ -7,7 +7,7 @@ import tempfile
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _WRAPPER = """
-#include "gemm_rules.h"
+#include "rules.h"
 extern "C" int split_wm(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).wm; }
 extern "C" int split_ks(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).ks; }
 """

@@ -234,7 +234,20 @@ def test_wide_beam_step_orders_ties_by_index(beam, k):
     """Every row of a sentence holds the same coarse scores, so a row's words tie with each other and with the other
     rows': the picks are decided by (higher score, then lower beam * vocab + word), through the per-row stage and the
     per-sentence merge by one wave (up to 64 candidates) and by four."""
-    V, batch = 2004, 3
+    _check_picks(2004, beam, k)
+
+
+# The per-row threshold of more than 16 picks: fewer words than picks need lanes (124 of 128), groups of one lane's words,
+# of several, of several registers (4100 on).  Rows of random scores, of nothing but ties, and in order of their scores
+# (falling and rising), whose best words are neighbours.
+@pytest.mark.parametrize("V", [36, 124, 128, 132, 1000, 2048, 4092, 4100, 8004])
+@pytest.mark.parametrize("beam,k", [(17, 17), (20, 20), (32, 32), (3, 32)])
+def test_wide_beam_thresholds(V, beam, k):
+    _check_picks(V, beam, k)
+
+
+def _check_picks(V, beam, k):
+    batch = 5
     cfg = _cfg(batch=batch, beam=beam, V=V, n_dec=1, self_pi=[1], encdec_pi=[1])
     gpu = hz.make_gpu(cfg, wl.make_weights(cfg, seed=3))
     src, lens = wl.make_source(cfg, 3)
@@ -242,6 +255,7 @@ def test_wide_beam_step_orders_ties_by_index(beam, k):
     rng = np.random.default_rng(7)
     rows = np.round(rng.normal(size=(batch, V)) * 2) / 2
     rows[1] = 0.0                                    # nothing but ties
+    rows[3], rows[4] = np.arange(V) / 64, -np.arange(V) / 64
     logits = torch.from_numpy(np.repeat(rows, beam, axis=0).astype(np.float32)).cuda()
     cum = torch.zeros(batch * beam, device="cuda")
     cum[2 * beam + beam // 2] = -np.inf              # a dead hypothesis
