@@ -453,6 +453,7 @@ template <typename T, int LPP> static hipError_t launch_lpp(const AttnParams& p0
 
 hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t stream) {
   if (p.rows <= 0 || p.lmax <= 0) return hipSuccess;
+  if (p.row_off && (p.self_mode || p.causal || !p.len || p.group_map)) return hipErrorInvalidValue;
   if (attention_ctx_mfma_fits(dtype, p)) return launch_attention_ctx_mfma(p, stream);
   // Long streams in a launch that has fewer of them than the chip has SIMDs are split over
   // several waves each (attention_split.hip); measured on the 12-layer, 256-step workload
@@ -462,13 +463,18 @@ hipError_t launch_attention(int dtype, const AttnParams& p, hipStream_t stream) 
   // wave per stream (at 2048 streams of <= 64 positions the split kernel's extra workgroup
   // barrier and LDS combine cost more than its shorter chains save: 8.4 vs 7.7 us), and so
   // are followers (their single pass over V is short already).
-  if (!p.apply && !p.row_off) {
+  // The encoder's own positions (ragged or not; a ragged batch counts by its padded size, as the lengths are on the
+  // device): one query per workgroup multiplies the waves by 16, which pays while the chip holds them -- encodes of 6
+  // layers, 4 heads of 128, 5 x 104 / 3 x 200 / 8 x 100 words 662 -> 649, 786 -> 775, 725 -> 771 us -- and where a
+  // stream has two chunks or more (bf16, 32-wide heads, 64 positions each: 5 x 104 225 -> 232, 4 x 128 232 -> 223).
+  // Elsewhere it saves up to 40 % (fp32, 2 heads of 128: 2 x 256 603 -> 375, 8 x 100 474 -> 431).
+  if (!p.apply) {
     const long streams = p.self_mode ? (long)p.rows * p.H : (long)p.groups * p.H * ((p.rpg + 3) / 4);
     if (p.self_mode && streams <= 1024 && p.lmax >= 128) return launch_attention_split(dtype, p, 2, false, stream);
-    if (!p.self_mode && !p.causal && p.rpg > 1 && streams < 1024 && p.lmax >= 96)
+    const bool pays = !p.self_queries || ((long)p.rows * p.H * p.dh <= 320000 && (dtype == 0 || p.dh >= 64 || p.lmax >= 128));
+    if (!p.self_mode && !p.causal && p.rpg > 1 && streams < 1024 && p.lmax >= 96 && pays)
       return launch_attention_split(dtype, p, 4, true, stream);
   }
-  if (p.row_off && (p.self_mode || p.causal || !p.len || p.group_map)) return hipErrorInvalidValue;
   if (p.lmax > 1024) return hipErrorInvalidValue;   // score rows must fit 64 KB of LDS
   if (p.ldk < 0 || p.ldv < 0 || p.ldk >= (1 << 24) || p.ldv >= (1 << 24)) return hipErrorInvalidValue;
   if (p.self_mode && p.ldk != p.ldv && !p.apply) return hipErrorInvalidValue;   // one offset table serves both caches

@@ -149,13 +149,16 @@ __global__ __launch_bounds__(kMaxWavesPerBlock * 64) void attention_kernel_split
     for (int i = 1; i < NQ; ++i) { qrow[i] = -1; nk[i] = 0; }
   } else {
     const int grp = rest;
-    slot_base = (long long)(p.group_map ? p.group_map[grp] : grp) * p.slot_stride;
+    slot_base = p.row_off ? (long long)p.row_off[grp] : (long long)(p.group_map ? p.group_map[grp] : grp) * p.slot_stride;
     const int nfull = p.len ? max(0, min(p.len[grp], p.lmax)) : p.n_fixed;
+    const int q_base = p.row_off ? (int)slot_base : grp * p.rpg;
+    const int q_n = p.row_off ? nfull : p.rpg;   // queries of the group
+    if (qb * NQ >= q_n) return;                  // whole block, before any barrier
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int li = qb * NQ + i;
-      if (li < p.rpg) {
-        qrow[i] = grp * p.rpg + li;
+      if (li < q_n) {
+        qrow[i] = q_base + li;
         nk[i] = p.causal ? min(nfull, li % p.causal + 1) : nfull;
         n = max(n, nk[i]);
       } else {

@@ -112,8 +112,8 @@ struct AttnParams {
   const int* group_map;             // grouped: memory of group g is slot group_map[g] (nullptr: g)
   const int* row_off;               // grouped, self-attention over ragged groups: the queries AND keys of group g are rows
                                     // row_off[g] .. row_off[g] + len[g] - 1 (instead of g * rpg and g * slot_stride on)
-  int self_queries;                 // grouped, with kv_packed: the queries are the group's own positions (the encoder), any number
-                                    // of them, and the weights of P V keep their 24 bits
+  int self_queries;                 // grouped: the queries are the group's own positions (the encoder), any number of them; on
+                                    // the matrix cores the weights of P V then keep their 24 bits
   int H, dh;
   int apply, emit, zero_tail;
   int lmax;                         // capacity of one score row (>= any n)

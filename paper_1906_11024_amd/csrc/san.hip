@@ -720,12 +720,12 @@ int san_encode(san_ctx* c, const int32_t* src_ids_dev, const int32_t* src_len_de
     a.len = c->src_len; a.rows = Ms; a.groups = batch; a.rpg = max_src; a.slot_stride = max_src;
     a.H = c->H; a.dh = c->dh; a.lmax = max_src; a.scale = scale;
     a.row_off = ragged ? c->enc_off : nullptr;
+    a.self_queries = 1;
     // bf16: on the matrix cores, from a copy of the layer's keys and values in fragment order, where the batch is large
     // enough for two launches to beat one
     if (ehead && c->enc_packed && Ms >= kEncMfmaMinRows) {
       LAUNCH(c, launch_pack_memory(a.K, a.ldk, a.V, a.ldv, batch, max_src, c->H, c->enc_packed, c->src_pad / 32, c->stream, a.row_off));
       a.kv_packed = c->enc_packed; a.kv_blocks = c->src_pad / 32;
-      a.self_queries = 1;
     }
     LAUNCH(c, launch_attention(c->dt, a, c->stream));
     if ((rc = gemm_ln(c, c->ab, d, e.wo, e.bo, Ms, d, c->x, e.ln1g, e.ln1b, c->x, nullptr))) return rc;

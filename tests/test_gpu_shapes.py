@@ -179,7 +179,10 @@ def test_activations_too_large_to_split(value):
 
 
 @pytest.mark.parametrize("dtype,batch,max_src,share,enc_pi", [("f32", 40, 61, "A", None), ("bf16", 33, 70, "S", None),
-                                                              ("f32", 20, 30, "A", [2, 1]), ("f32", 1030, 5, "A", None)])
+                                                              ("f32", 20, 30, "A", [2, 1]), ("f32", 1030, 5, "A", None),
+                                                              # few long streams: each is split over four waves
+                                                              ("f32", 6, 104, "A", None), ("bf16", 6, 104, "S", None),
+                                                              ("f32", 5, 130, "A", [2, 1])])
 def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_pi):
     """Lengths 0 .. max_src.  The rows of a product or a LayerNorm do not depend on each other, so leaving out the
     padding changes no bit (debug = 1 keeps the padded route); a few sentences are checked against the oracle."""
