@@ -153,21 +153,27 @@ struct AanFuse {
 hipError_t launch_embed(int dtype, const int* tok, int tok_stride, int rpg, const void* emb, const float* pe,
                         const int* t_dev, void* x, int rows, int d, int vocab, float scale, int* last_tok,
                         int* anc, int ld_anc, hipStream_t stream, const AanFuse* aan = nullptr,
-                        const int* row_off = nullptr);
-// off[g] = sum of the first g lengths (each clamped to [0, n_pos]), g <= groups: where the words of a ragged batch lie
-// when its padding is left out.  launch_embed with row_off = off writes the words of hypothesis (sentence) g there.
-hipError_t launch_ragged_offsets(const int* len, int groups, int n_pos, int* off, hipStream_t stream);
-// dst[g * n_pos + i] = src[off[g] + i] for i < off[g + 1] - off[g], zero rows from there to n_pos (rows of d elements)
-hipError_t launch_unpack_rows(int dtype, const void* src, const int* off, void* dst, int groups, int n_pos, int d,
-                              hipStream_t stream);
+                        const int* row_off = nullptr, int* slot = nullptr);
+// The state a batch of `groups` sentences starts from: len[g] = len0[g], group_map[g] = g, done[0 .. n_done) = 0, *t = 0;
+// off (optional) [groups + 1]: off[g] = sum of the first g lengths (each clamped to [0, n_pos]), where the words of a
+// ragged batch lie when its padding is left out.  launch_embed with row_off = off writes the words of sentence g there,
+// and to slot [groups * n_pos] the padded rows in that order: the words' first, then the padding's.
+struct EncodeBegin {
+  const int* len0; int* len; int* group_map;
+  int* done; int n_done; int* t;
+  int* off; int groups, n_pos;
+};
+hipError_t launch_encode_begin(const EncodeBegin& e, hipStream_t stream);
 
 // out[m] = LayerNorm(sum_s part[s][m] + bias + res[m]) * g + b  (row-wise over n);
 // part is [nsplit][M][ldp] and may point at a column offset of a wider buffer
-// stage2: see LnStage2
+// stage2: see LnStage2.  ragged: rows from *m_dev on are padding; slot (optional): row m goes to row slot[m] of out
+// instead, zeros for the padding (from the back-to-back order to the padded one)
+struct RaggedRows { const int* m_dev; const int* slot; };
 hipError_t launch_ln_reduce(int dtype, const float* part, int nsplit, int ldp, const void* bias, const void* res, int ldr,
                             const void* gamma, const void* beta, void* out, int ldo, float* out_f32, int M, int n,
                             float eps, hipStream_t stream, const LnStage2* stage2 = nullptr,
-                            const AanFuse* aan = nullptr, const int* m_dev = nullptr);   // m_dev: see GemmParams
+                            const AanFuse* aan = nullptr, const RaggedRows* ragged = nullptr);
 
 // start of a decode step: last_tok[r] = tok[r]; anc[r][t] = r; hist[r][t] = tok[r]
 hipError_t launch_step_begin(const int* tok, int* last_tok, int* anc, int* hist, int ld, const int* t_dev, int rows,

@@ -31,15 +31,17 @@ template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const int* tok, int tok_stride, int rpg, const T* emb,
                                                     const float* pe, const int* t_dev, T* x, int rows, int d,
                                                     int vocab, float scale, int* last_tok, int* anc, int ld_anc,
-                                                    AanFuse aan, const int* row_off) {
+                                                    AanFuse aan, const int* row_off, int* slot) {
   int r = blockIdx.x;
   if (r >= rows) return;
   const int hyp = r / rpg, i = r % rpg;
   int id = tok[(size_t)hyp * tok_stride + i];
   if (row_off) {   // ragged batch without its padding
-    const int first = row_off[hyp];
-    if (i >= row_off[hyp + 1] - first) return;
-    r = first + i;
+    const int first = row_off[hyp], next = row_off[hyp + 1];
+    const int to = i < next - first ? first + i : row_off[rows / rpg] + r - next;   // r - next: padding before this position
+    if (threadIdx.x == 0) slot[to] = r;
+    if (i >= next - first) return;
+    r = to;
   }
   const int pos = t_dev ? *t_dev : i;
   if (threadIdx.x == 0) {
@@ -61,71 +63,60 @@ __global__ __launch_bounds__(256) void embed_kernel(const int* tok, int tok_stri
 
 hipError_t launch_embed(int dtype, const int* tok, int tok_stride, int rpg, const void* emb, const float* pe,
                         const int* t_dev, void* x, int rows, int d, int vocab, float scale, int* last_tok,
-                        int* anc, int ld_anc, hipStream_t stream, const AanFuse* aan, const int* row_off) {
+                        int* anc, int ld_anc, hipStream_t stream, const AanFuse* aan, const int* row_off, int* slot) {
   if (rows <= 0) return hipSuccess;
   AanFuse af{};
   if (aan) af = *aan;
   if (af.sum && (!t_dev || rpg != 1)) return hipErrorInvalidValue;   // cached decoding only
-  if (row_off && (t_dev || last_tok || anc)) return hipErrorInvalidValue;   // the encoder only
+  if (row_off && (t_dev || last_tok || anc || !slot || rows % rpg)) return hipErrorInvalidValue;   // the encoder only
   const int threads = d / 4 >= 256 ? 256 : (d / 4 >= 128 ? 128 : 64);
   if (dtype == 1)
     hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(rows), dim3(threads), 0, stream, tok, tok_stride, rpg,
                        (const bf16_t*)emb, pe, t_dev, (bf16_t*)x, rows, d, vocab, scale, last_tok, anc, ld_anc, af,
-                       row_off);
+                       row_off, slot);
   else
     hipLaunchKernelGGL(embed_kernel<float>, dim3(rows), dim3(threads), 0, stream, tok, tok_stride, rpg,
                        (const float*)emb, pe, t_dev, (float*)x, rows, d, vocab, scale, last_tok, anc, ld_anc, af,
-                       row_off);
+                       row_off, slot);
   return hipGetLastError();
 }
 
-// ------------------------------------------------------- ragged batches (encoder)
-// One block: every thread adds up a run of groups, the runs' sums are scanned in LDS.
-__global__ __launch_bounds__(1024) void ragged_offsets_kernel(const int* len, int groups, int n_pos, int* off) {
+// ------------------------------------------------------- start of an encode, ragged batches
+// One block; every thread takes a run of sentences (their lengths' sums are scanned in LDS).  Bound by its launch; the
+// two copies and two fills that it stands for were four stream operations of 2 us and more (an encode of 32 x 16 words by
+// the tiny model, which has no padding to leave out: 85 us with them and a kernel for the offsets, now 70).
+__global__ __launch_bounds__(1024) void encode_begin_kernel(EncodeBegin e) {
   __shared__ int sums[1024];
-  const int per = (groups + 1023) / 1024, g0 = min((int)threadIdx.x * per, groups), g1 = min(g0 + per, groups);
+  const int tid = threadIdx.x;
+  const int per = (e.groups + 1023) / 1024, g0 = min(tid * per, e.groups), g1 = min(g0 + per, e.groups);
   int s = 0;
-  for (int g = g0; g < g1; ++g) s += max(0, min(len[g], n_pos));
-  sums[threadIdx.x] = s;
+  for (int g = g0; g < g1; ++g) {
+    const int n = e.len0[g];
+    e.len[g] = n;
+    e.group_map[g] = g;
+    s += max(0, min(n, e.n_pos));
+  }
+  for (int i = tid; i < e.n_done; i += 1024) e.done[i] = 0;
+  if (tid == 0) *e.t = 0;
+  if (!e.off) return;   // uniform
+  sums[tid] = s;
   __syncthreads();
   for (int step = 1; step < 1024; step *= 2) {
-    const int add = (int)threadIdx.x >= step ? sums[threadIdx.x - step] : 0;
+    const int add = tid >= step ? sums[tid - step] : 0;
     __syncthreads();
-    sums[threadIdx.x] += add;
+    sums[tid] += add;
     __syncthreads();
   }
-  int at = sums[threadIdx.x] - s;
+  int at = sums[tid] - s;
   for (int g = g0; g < g1; ++g) {
-    off[g] = at;
-    at += max(0, min(len[g], n_pos));
+    e.off[g] = at;
+    at += max(0, min(e.len0[g], e.n_pos));
   }
-  if (threadIdx.x == 1023) off[groups] = sums[1023];
+  if (tid == 1023) e.off[e.groups] = sums[1023];
 }
-hipError_t launch_ragged_offsets(const int* len, int groups, int n_pos, int* off, hipStream_t stream) {
-  if (groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ragged_offsets_kernel, dim3(1), dim3(1024), 0, stream, len, groups, n_pos, off);
-  return hipGetLastError();
-}
-
-template <typename T> __global__ __launch_bounds__(256) void unpack_rows_kernel(const T* src, const int* off, T* dst, int n_pos, int d) {
-  const int r = blockIdx.x, g = r / n_pos, i = r - g * n_pos;
-  const int first = off[g];
-  const bool live = i < off[g + 1] - first;
-  for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) v = load4(src + (size_t)(first + i) * d + c);
-    store4(dst + (size_t)r * d + c, v);
-  }
-}
-hipError_t launch_unpack_rows(int dtype, const void* src, const int* off, void* dst, int groups, int n_pos, int d,
-                              hipStream_t stream) {
-  const size_t rows = (size_t)groups * n_pos;
-  if (!rows) return hipSuccess;
-  const dim3 block(d / 4 >= 256 ? 256 : (d / 4 >= 128 ? 128 : 64));
-  if (dtype == 1)
-    hipLaunchKernelGGL(unpack_rows_kernel<bf16_t>, dim3((unsigned)rows), block, 0, stream, (const bf16_t*)src, off, (bf16_t*)dst, n_pos, d);
-  else
-    hipLaunchKernelGGL(unpack_rows_kernel<float>, dim3((unsigned)rows), block, 0, stream, (const float*)src, off, (float*)dst, n_pos, d);
+hipError_t launch_encode_begin(const EncodeBegin& e, hipStream_t stream) {
+  if (e.groups <= 0) return hipSuccess;
+  hipLaunchKernelGGL(encode_begin_kernel, dim3(1), dim3(1024), 0, stream, e);
   return hipGetLastError();
 }
 
@@ -214,13 +205,20 @@ __global__ __launch_bounds__(kLnMaxWaves * 64) void ln_reduce_kernel(const float
                                                                      const T* bias, const T* res, int ldr,
                                                                      const T* gamma, const T* beta, T* out, int ldo,
                                                                      float* out_f32, int M, int n, float eps,
-                                                                     LnStage2 s2, AanFuse aan, const int* m_dev) {
+                                                                     LnStage2 s2, AanFuse aan, RaggedRows rag) {
   __shared__ float slots[4 * kLnMaxWaves];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
   const int m = blockIdx.x;
-  if (RAGGED && m >= *m_dev) return;   // padding of a ragged batch
   const int c = threadIdx.x * 4;
   const bool active = c < n;
+  int m_out = m;
+  if (RAGGED) {
+    if (rag.slot) m_out = rag.slot[m];
+    if (m >= *rag.m_dev) {             // padding of a ragged batch
+      if (rag.slot && active) store4(out + (size_t)m_out * ldo + c, make_float4(0.f, 0.f, 0.f, 0.f));
+      return;
+    }
+  }
   const int cc = active ? c : 0;   // inactive threads load column 0 and drop it
   const float4 g1 = load4(gamma + cc), b1 = load4(beta + cc);
   float4 g2 = g1, b2 = b1, u2 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -244,7 +242,7 @@ __global__ __launch_bounds__(kLnMaxWaves * 64) void ln_reduce_kernel(const float
     y = layer_norm_vec(y1, active, n, g2, b2, eps, slots + 2 * kLnMaxWaves, wid, lane, nwaves);
   }
   if (active) {
-    store4(out + (size_t)m * ldo + c, y);
+    store4(out + (size_t)m_out * ldo + c, y);
     if (out_f32) *reinterpret_cast<float4*>(out_f32 + (size_t)m * n + c) = y;
     if (aan.sum) aan_accumulate<T>(aan, m, c, n, y);   // the next layer is an average-attention layer
   }
@@ -309,9 +307,17 @@ __device__ __forceinline__ void layer_norm_row(float4 (&v)[NV], const bool (&act
 template <typename T, int NV, bool RAGGED>
 __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nsplit, int ldp, const T* bias, const T* res, int ldr,
                                                      const T* gamma, const T* beta, T* out, int ldo, float* out_f32, int M, int n,
-                                                     float eps, LnStage2 s2, AanFuse aan, const int* m_dev) {
+                                                     float eps, LnStage2 s2, AanFuse aan, RaggedRows rag) {
   const int m = blockIdx.x;
-  if (RAGGED && m >= *m_dev) return;
+  int m_out = m;
+  if (RAGGED) {
+    if (rag.slot) m_out = rag.slot[m];
+    if (m >= *rag.m_dev) {
+      if (rag.slot)
+        for (int c = (int)threadIdx.x * 4; c < n; c += 256) store4(out + (size_t)m_out * ldo + c, make_float4(0.f, 0.f, 0.f, 0.f));
+      return;
+    }
+  }
   int col[NV];
   bool act[NV];
   float4 g1[NV], b1[NV], g2[NV], b2[NV], u2[NV], v[NV];
@@ -344,7 +350,7 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nspl
 #pragma unroll
   for (int i = 0; i < NV; ++i)
     if (act[i]) {
-      store4(out + (size_t)m * ldo + col[i], v[i]);
+      store4(out + (size_t)m_out * ldo + col[i], v[i]);
       if (out_f32) *reinterpret_cast<float4*>(out_f32 + (size_t)m * n + col[i]) = v[i];
       if (aan.sum) aan_accumulate<T>(aan, m, col[i], n, v[i]);
     }
@@ -352,24 +358,26 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nspl
 
 hipError_t launch_ln_reduce(int dtype, const float* part, int nsplit, int ldp, const void* bias, const void* res, int ldr,
                             const void* gamma, const void* beta, void* out, int ldo, float* out_f32, int M, int n,
-                            float eps, hipStream_t stream, const LnStage2* stage2, const AanFuse* aan, const int* m_dev) {
+                            float eps, hipStream_t stream, const LnStage2* stage2, const AanFuse* aan, const RaggedRows* ragged) {
   if (M <= 0) return hipSuccess;
   if (n <= 0 || n > kLnMaxWaves * 256 || n % 4) return hipErrorInvalidValue;
   LnStage2 s2{};
   if (stage2) s2 = *stage2;
   AanFuse af{};
   if (aan) af = *aan;
+  RaggedRows rag{};
+  if (ragged) rag = *ragged;
   dim3 grid(M), block(64 * ((n / 4 + 63) / 64));
   auto one_of = [](int k) { return k == 1 || k == 2 || k == 4 || k == 8 || k == 16; };
   if (n <= kLnWaveCols && one_of(nsplit) && (!s2.part || one_of(s2.nsplit))) {
 #define SAN_LN(T, RAGGED)                                                                                              \
   hipLaunchKernelGGL((ln_wave_kernel<T, 2, RAGGED>), grid, dim3(64), 0, stream, part, nsplit, ldp, (const T*)bias,      \
-                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, m_dev)
+                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, rag)
     if (dtype == 1) {
-      if (m_dev) SAN_LN(bf16_t, true);
+      if (rag.m_dev) SAN_LN(bf16_t, true);
       else SAN_LN(bf16_t, false);
     } else {
-      if (m_dev) SAN_LN(float, true);
+      if (rag.m_dev) SAN_LN(float, true);
       else SAN_LN(float, false);
     }
 #undef SAN_LN
@@ -377,12 +385,12 @@ hipError_t launch_ln_reduce(int dtype, const float* part, int nsplit, int ldp, c
   }
 #define SAN_LN(T, RAGGED)                                                                                              \
   hipLaunchKernelGGL((ln_reduce_kernel<T, RAGGED>), grid, block, 0, stream, part, nsplit, ldp, (const T*)bias,         \
-                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, m_dev)
+                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, rag)
   if (dtype == 1) {
-    if (m_dev) SAN_LN(bf16_t, true);
+    if (rag.m_dev) SAN_LN(bf16_t, true);
     else SAN_LN(bf16_t, false);
   } else {
-    if (m_dev) SAN_LN(float, true);
+    if (rag.m_dev) SAN_LN(float, true);
     else SAN_LN(float, false);
   }
 #undef SAN_LN

@@ -140,6 +140,7 @@ struct san_ctx {
   int* group_map = nullptr;    // [max_batch] encode-time index of each current sentence
   void* enc_packed = nullptr;  // bf16, 64-wide heads: keys and values of one encoder layer in MFMA fragment order
   int* enc_off = nullptr;      // [max_batch + 1] first row of each sentence while the encoder runs without padding
+  int* enc_slot = nullptr;     // [max_batch * max_src_len] their padded rows in that order (launch_embed)
   const int* m_dev = nullptr;  // set while it does: the number of rows (enc_off[batch]); null otherwise
   int* iota_dev = nullptr;     // 0, 1, 2, ... [max(rows_max, max_batch)]
   int* keep_dev = nullptr;     // [max_batch]
@@ -325,7 +326,7 @@ int wtensor(san_ctx* c, void** dst, const void* blob, size_t off, size_t n) {
 }
 
 // Padded rows from which the encoder runs without padding (san_encode).  Below, its launches are bound by their fixed
-// cost, and the two extra ones (offsets, unpacking: 3 us each) cost more than fewer rows save.
+// cost, and the tests for the row count (0.3 us a launch) cost more than fewer rows save.
 constexpr int kRaggedMinRows = 512;
 // Padded rows from which the bf16 encoder's attention runs on the matrix cores (cfg.debug keeps the general kernel: it is
 // the cross-check, and copies of it and of the decoder's attention are compared with each other).
@@ -368,22 +369,24 @@ int gemm_ln(san_ctx* c, const void* A, int lda, const void* W, const void* bias,
   }
   const int k0 = c->kind;
   c->kind = SAN_K_LN;
+  const RaggedRows ragged{c->m_dev, out != c->x ? c->enc_slot : nullptr};   // not in place: back to padded rows
   LAUNCH(c, launch_ln_reduce(c->dt, c->part, ks, N, bias, res, N, g, b, out, N, dbg, M, N, c->cfg.ln_eps, c->stream,
-                             nullptr, aan, c->m_dev));
+                             nullptr, aan, c->m_dev ? &ragged : nullptr));
   c->kind = k0;
   return SAN_OK;
 }
 
 // next_aan: the layer that consumes this block's output is an average-attention layer of a
 // cached decode; its running sum / mean / gate input are produced by the LayerNorm launch
-int ffn_block(san_ctx* c, const DecLayer* L, const EncLayer* E, int M, float* dbg, const AanFuse* next_aan = nullptr) {
+int ffn_block(san_ctx* c, const DecLayer* L, const EncLayer* E, int M, float* dbg, const AanFuse* next_aan = nullptr,
+              void* out = nullptr) {
   const void* w1 = L ? L->w1 : E->w1; const void* b1 = L ? L->b1 : E->b1;
   const void* w2 = L ? L->w2 : E->w2; const void* b2 = L ? L->b2 : E->b2;
   const void* g = L ? L->ln3g : E->ln2g; const void* b = L ? L->ln3b : E->ln2b;
   if (L) c->kind = SAN_K_FFN;
   int rc = gemm(c, c->x, c->d, w1, b1, M, c->F, c->d, 1, 0, c->hb, c->F);
   if (rc) return rc;
-  return gemm_ln(c, c->hb, c->F, w2, b2, M, c->F, c->x, g, b, c->x, dbg, nullptr, next_aan);
+  return gemm_ln(c, c->hb, c->F, w2, b2, M, c->F, c->x, g, b, out ? out : c->x, dbg, nullptr, next_aan);
 }
 
 int dbg_copy(san_ctx* c, const void* src, int lds, float* dst, int rows) {
@@ -573,6 +576,7 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
     TRY(dalloc(c, (void**)&c->group_map, (size_t)cfg->max_batch * 4, false));
     TRY(dalloc(c, (void**)&c->keep_dev, (size_t)cfg->max_batch * 4, false));
     TRY(dalloc(c, (void**)&c->enc_off, ((size_t)cfg->max_batch + 1) * 4, false));
+    if (c->rows_src_max >= kRaggedMinRows) TRY(dalloc(c, (void**)&c->enc_slot, (size_t)c->rows_src_max * 4, false));
     if (c->dt == SAN_BF16 && c->dh == 64 && !cfg->debug && c->rows_src_max >= kEncMfmaMinRows)
       TRY(dalloc(c, &c->enc_packed, (size_t)cfg->max_batch * c->H * (c->src_pad / 32) * 8192, false));
     {
@@ -680,9 +684,7 @@ int san_encode(san_ctx* c, const int32_t* src_ids_dev, const int32_t* src_len_de
   c->t = -1;
   int rc;
   c->kind = SAN_K_MISC;
-  HIP_TRY(c, hipMemcpyAsync(c->src_len, src_len_dev, (size_t)batch * 4, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->src_len0, src_len_dev, (size_t)batch * 4, hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->group_map, c->iota_dev, (size_t)batch * 4, hipMemcpyDeviceToDevice, c->stream));
   c->batch = batch;   // the encoder below runs on the whole batch
   c->batch_enc = batch;
   c->active.resize(batch);
@@ -695,12 +697,13 @@ int san_encode(san_ctx* c, const int32_t* src_ids_dev, const int32_t* src_len_de
     san_ctx* c;
     ~RowCount() { c->m_dev = nullptr; }
   } row_count{c};
-  if (ragged) {
-    LAUNCH(c, launch_ragged_offsets(c->src_len, batch, max_src, c->enc_off, c->stream));
-    c->m_dev = c->enc_off + batch;
-  }
+  LAUNCH(c, launch_encode_begin(EncodeBegin{c->src_len0, c->src_len, c->group_map, c->done_dev, c->cfg.max_batch + 1, c->t_dev,
+                                            ragged ? c->enc_off : nullptr, batch, max_src}, c->stream));
+  if (ragged) c->m_dev = c->enc_off + batch;
   LAUNCH(c, launch_embed(c->dt, src_ids_dev, max_src, max_src, c->src_emb, c->pe, nullptr, c->x, Ms, d, c->V,
-                         (float)std::sqrt((double)d), nullptr, nullptr, 0, c->stream, nullptr, ragged ? c->enc_off : nullptr));
+                         (float)std::sqrt((double)d), nullptr, nullptr, 0, c->stream, nullptr, ragged ? c->enc_off : nullptr,
+                         ragged ? c->enc_slot : nullptr));
+  void* const enc_out = ragged ? c->ab : c->x;   // the memories keep a slot of max_src positions per sentence
   for (size_t li = 0; li < c->enc.size(); ++li) {
     const EncLayer& e = c->enc[li];
     const bool ehead = e.head == (int)li;
@@ -729,17 +732,11 @@ int san_encode(san_ctx* c, const int32_t* src_ids_dev, const int32_t* src_len_de
     }
     LAUNCH(c, launch_attention(c->dt, a, c->stream));
     if ((rc = gemm_ln(c, c->ab, d, e.wo, e.bo, Ms, d, c->x, e.ln1g, e.ln1b, c->x, nullptr))) return rc;
-    if ((rc = ffn_block(c, nullptr, &e, Ms, nullptr))) return rc;
+    if ((rc = ffn_block(c, nullptr, &e, Ms, nullptr, nullptr, li + 1 == c->enc.size() ? enc_out : nullptr))) return rc;
     c->kind = SAN_K_MISC;
   }
   if (c->dbg_enc) LAUNCH(c, launch_to_f32(c->dt, c->x, d, c->dbg_enc, Ms, d, c->stream));
-  // the memories keep a slot of max_src positions per sentence
-  const void* enc_out = c->x;
   c->m_dev = nullptr;
-  if (ragged) {
-    LAUNCH(c, launch_unpack_rows(c->dt, c->x, c->enc_off, c->ab, batch, max_src, d, c->stream));
-    enc_out = c->ab;
-  }
   // encoder-decoder keys/values: block heads get [K;V]; in mode S every follower gets its own V
   for (DecLayer& L : c->dec) {
     if (!L.mem) continue;
@@ -749,8 +746,6 @@ int san_encode(san_ctx* c, const int32_t* src_ids_dev, const int32_t* src_len_de
       LAUNCH(c, launch_pack_memory(L.mem, N, (char*)L.mem + (size_t)d * c->esz, N, batch, max_src, c->H, L.mem_packed,
                                    c->src_pad / 32, c->stream));
   }
-  HIP_TRY(c, hipMemsetAsync(c->t_dev, 0, 4, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->done_dev, 0, ((size_t)c->cfg.max_batch + 1) * 4, c->stream));
   c->batch = batch; c->max_src = max_src; c->t = 0;
   c->graph_rows = 0;   // a captured step graph is tied to the batch shape
   return prof_flush(c);

@@ -178,15 +178,17 @@ def test_activations_too_large_to_split(value):
     assert np.array_equal(got, _logits_of(cfg, row, w_out, 2))
 
 
-@pytest.mark.parametrize("dtype,batch,max_src,share,enc_pi", [("f32", 40, 61, "A", None), ("bf16", 33, 70, "S", None),
-                                                              ("f32", 20, 30, "A", [2, 1]), ("f32", 1030, 5, "A", None),
-                                                              # few long streams: each is split over four waves
-                                                              ("f32", 6, 104, "A", None), ("bf16", 6, 104, "S", None),
-                                                              ("f32", 5, 130, "A", [2, 1])])
-def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_pi):
+@pytest.mark.parametrize("dtype,batch,max_src,share,enc_pi,d,H", [("f32", 40, 61, "A", None, 128, 4), ("bf16", 33, 70, "S", None, 128, 4),
+                                                                  ("f32", 20, 30, "A", [2, 1], 128, 4), ("f32", 1030, 5, "A", None, 128, 4),
+                                                                  # few long streams: each is split over four waves
+                                                                  ("f32", 6, 104, "A", None, 128, 4), ("bf16", 6, 104, "S", None, 128, 4),
+                                                                  ("f32", 5, 130, "A", [2, 1], 128, 4),
+                                                                  # rows wider than the LayerNorm of one wave takes
+                                                                  ("f32", 18, 61, "A", None, 576, 9), ("bf16", 18, 61, "A", None, 640, 20)])
+def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_pi, d, H):
     """Lengths 0 .. max_src.  The rows of a product or a LayerNorm do not depend on each other, so leaving out the
     padding changes no bit (debug = 1 keeps the padded route); a few sentences are checked against the oracle."""
-    cfg = _cfg(n_enc=3 if enc_pi else 2, n_dec=2, d=128, H=4, dtype=dtype, batch=batch, src_len=(1, max_src), steps=3, self_pi=[2],
+    cfg = _cfg(n_enc=3 if enc_pi else 2, n_dec=2, d=d, H=H, dtype=dtype, batch=batch, src_len=(1, max_src), steps=3, self_pi=[2],
                encdec_pi=[2])
     w = wl.make_weights(cfg, seed=9, sharp=4.0)
     src, lens = wl.make_source(cfg, 9)
@@ -199,6 +201,8 @@ def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_
     got = []
     for debug in (0, 1):
         gpu = hz.make_gpu(cfg, w, share=share, debug=debug, **kw)
+        # what an earlier batch without padding left behind has no part in it
+        gpu.encode(torch.from_numpy(src % 50 + 3).cuda(), torch.full((batch,), max_src, dtype=torch.int32, device="cuda"))
         got.append(hz.gpu_free_run(gpu, src, lens, 1, cfg["steps"], keep_logits=True)["logits"])
         gpu.close()
     for t in range(cfg["steps"]):
