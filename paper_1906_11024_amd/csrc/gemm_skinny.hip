@@ -247,16 +247,6 @@ __global__ __launch_bounds__(kSkWaves * 64) void skinny_kernel(GemmParams p, LnI
 // the layer is then requested at once); 64 below, as the candidate epilogue works on 64 columns or more.
 int gemm_skinny_cand_n(int N) { return N >= 16384 ? 128 : 64; }
 
-int gemm_skinny_ksplit(int N, int K, int dtype) {
-  // a wave keeps two units or more, and splitting stops at half a block per CU: what a split saves in load time it
-  // costs in partials, which every block of the consumer reads
-  const int units = K * (dtype == 1 ? 2 : 4) / kUnit;
-  const int tiles = (N + 15) / 16;
-  int ks = 1;
-  while (ks < 4 && tiles * ks < 128 && units % (ks * 2) == 0 && units / (ks * 2) >= 2 * kSkWaves) ks *= 2;
-  return ks;
-}
-
 template <typename T, int NB, int NV, bool S2, bool CAND>
 static hipError_t launch_one(const GemmParams& p, const LnInput& ln, hipStream_t stream) {
   size_t smem = ((size_t)kSkWaves * NB * 256 + (CAND ? 16 * (16 * NB + 4) : 0)) * 4;

@@ -45,9 +45,6 @@ constexpr int kGemmRelu = 1, kGemmRagged = 2;
 constexpr int kGemmCandMaxK = 8;
 // plain: fp32 without splitting into bf16 parts (gemm_split.hip)
 hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t stream);
-// split factor that fills the chip for an M x N x K product (1 when the tiles
-// alone already do)
-int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain);
 int gemm_cand_tile_n(int M, int N, int K, int dtype);
 
 // fp32 only: the same product through the bf16 matrix cores with every operand split into three bf16 parts
@@ -75,10 +72,8 @@ struct LnInput {
   void* x_out;
   LnStage2 s2;
 };
-constexpr int kSkinnyRows = 16, kSkinnyLnWidth = 1024;
 int gemm_skinny_cand_n(int N);   // column tile of out_kind 3 on this route
 hipError_t launch_gemm_skinny(int dtype, const GemmParams& p, const LnInput& ln, hipStream_t stream);
-int gemm_skinny_ksplit(int N, int K, int dtype);
 
 // ------------------------------------------------------------------ attention
 // One kernel for every attention in the model.  A wave owns one head of one

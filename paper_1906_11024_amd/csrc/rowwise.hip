@@ -199,15 +199,19 @@ __device__ __forceinline__ float4 gather_update(const float* part, int nsplit, s
   return make_float4(sum.x + a.x, sum.y + a.y, sum.z + a.z, sum.w + a.w);
 }
 
-// RAGGED: a kernel of its own, because the others would pay for the test (0.3 us: their loads wait behind it)
-template <typename T, bool RAGGED>
+// A launch costs what its chain of dependent fetches costs, and that begins with the code: each combination has a kernel
+// of its own, so that the lines it touches lie together.  With the branches for one or two stages and 1 to 16 splits in
+// one kernel of 8 KB a launch took 0.2 to 0.3 us more, by where the kernel happened to lie (a step at 768 columns, bf16,
+// 17 to 512 rows: 243-443 us, now 235-426).  NS, NS2: splits of the two stages, 0 for any number; NS2 < 0: one stage.
+// RAGGED: the others would pay for the test (0.3 us: their loads wait behind it).
+template <typename T, bool RAGGED, int NS, int NS2>
 __global__ __launch_bounds__(kLnMaxWaves * 64) void ln_reduce_kernel(const float* part, int nsplit, int ldp,
                                                                      const T* bias, const T* res, int ldr,
                                                                      const T* gamma, const T* beta, T* out, int ldo,
                                                                      float* out_f32, int M, int n, float eps,
                                                                      LnStage2 s2, AanFuse aan, RaggedRows rag) {
   __shared__ float slots[4 * kLnMaxWaves];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nwaves = (n + 255) >> 8;
   const int m = blockIdx.x;
   const int c = threadIdx.x * 4;
   const bool active = c < n;
@@ -222,16 +226,22 @@ __global__ __launch_bounds__(kLnMaxWaves * 64) void ln_reduce_kernel(const float
   const int cc = active ? c : 0;   // inactive threads load column 0 and drop it
   const float4 g1 = load4(gamma + cc), b1 = load4(beta + cc);
   float4 g2 = g1, b2 = b1, u2 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (s2.part) {
+  if constexpr (NS2 >= 0) {
     g2 = load4(reinterpret_cast<const T*>(s2.gamma) + cc);
     b2 = load4(reinterpret_cast<const T*>(s2.beta) + cc);
-    u2 = gather_update<T>(s2.part + (size_t)m * s2.ldp + cc, s2.nsplit, (size_t)M * s2.ldp,
-                          reinterpret_cast<const T*>(s2.bias) + cc, (const T*)nullptr, gamma + cc);
+    const float* const p2 = s2.part + (size_t)m * s2.ldp + cc;
+    const T* const bias2 = reinterpret_cast<const T*>(s2.bias) + cc;
+    if constexpr (NS2 > 0) u2 = gather_fixed<T, NS2>(p2, (size_t)M * s2.ldp, bias2, (const T*)nullptr, gamma + cc);
+    else u2 = gather_update<T>(p2, s2.nsplit, (size_t)M * s2.ldp, bias2, (const T*)nullptr, gamma + cc);
   }
-  const float4 v = gather_update<T>(part + (size_t)m * ldp + cc, nsplit, (size_t)M * ldp, bias ? bias + cc : nullptr,
-                                    res ? res + (size_t)m * ldr + cc : nullptr, gamma + cc);
+  const float* const p1 = part + (size_t)m * ldp + cc;
+  const T* const b_in = bias ? bias + cc : nullptr;
+  const T* const r_in = res ? res + (size_t)m * ldr + cc : nullptr;
+  float4 v;
+  if constexpr (NS > 0) v = gather_fixed<T, NS>(p1, (size_t)M * ldp, b_in, r_in, gamma + cc);
+  else v = gather_update<T>(p1, nsplit, (size_t)M * ldp, b_in, r_in, gamma + cc);
   float4 y = layer_norm_vec(v, active, n, g1, b1, eps, slots, wid, lane, nwaves);
-  if (s2.part) {
+  if constexpr (NS2 >= 0) {
     // second sub-layer without a GEMM of its own in between (an enc-dec follower
     // whose projected context was computed at the block head): add the second
     // update to the first LayerNorm's output and normalise again.  That output was
@@ -304,7 +314,7 @@ __device__ __forceinline__ void layer_norm_row(float4 (&v)[NV], const bool (&act
     v[i] = make_float4((v[i].x - mean) * rstd * g[i].x + b[i].x, (v[i].y - mean) * rstd * g[i].y + b[i].y,
                        (v[i].z - mean) * rstd * g[i].z + b[i].z, (v[i].w - mean) * rstd * g[i].w + b[i].w);
 }
-template <typename T, int NV, bool RAGGED>
+template <typename T, int NV, bool RAGGED, int NS, int NS2>
 __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nsplit, int ldp, const T* bias, const T* res, int ldr,
                                                      const T* gamma, const T* beta, T* out, int ldo, float* out_f32, int M, int n,
                                                      float eps, LnStage2 s2, AanFuse aan, RaggedRows rag) {
@@ -329,18 +339,22 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nspl
     g1[i] = load4(gamma + col[i]);
     b1[i] = load4(beta + col[i]);
   }
-  if (s2.part) {
+  if constexpr (NS2 >= 0) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       g2[i] = load4(reinterpret_cast<const T*>(s2.gamma) + col[i]);
       b2[i] = load4(reinterpret_cast<const T*>(s2.beta) + col[i]);
     }
-    gather_row<T, NV>(u2, s2.part + (size_t)m * s2.ldp, s2.nsplit, (size_t)M * s2.ldp, reinterpret_cast<const T*>(s2.bias),
-                      (const T*)nullptr, gamma, col);
+    const float* const p2 = s2.part + (size_t)m * s2.ldp;
+    const T* const bias2 = reinterpret_cast<const T*>(s2.bias);
+    if constexpr (NS2 > 0) gather_row<T, NV, NS2>(u2, p2, (size_t)M * s2.ldp, bias2, (const T*)nullptr, gamma, col);
+    else gather_row<T, NV>(u2, p2, s2.nsplit, (size_t)M * s2.ldp, bias2, (const T*)nullptr, gamma, col);
   }
-  gather_row<T, NV>(v, part + (size_t)m * ldp, nsplit, (size_t)M * ldp, bias, res ? res + (size_t)m * ldr : nullptr, gamma, col);
+  const T* const r_in = res ? res + (size_t)m * ldr : nullptr;
+  if constexpr (NS > 0) gather_row<T, NV, NS>(v, part + (size_t)m * ldp, (size_t)M * ldp, bias, r_in, gamma, col);
+  else gather_row<T, NV>(v, part + (size_t)m * ldp, nsplit, (size_t)M * ldp, bias, r_in, gamma, col);
   layer_norm_row<NV>(v, act, n, g1, b1, eps);
-  if (s2.part) {   // see ln_reduce_kernel
+  if constexpr (NS2 >= 0) {   // see ln_reduce_kernel
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       v[i] = make_float4(to_f32(from_f32<T>(v[i].x)) + u2[i].x, to_f32(from_f32<T>(v[i].y)) + u2[i].y,
@@ -356,45 +370,69 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(const float* part, int nspl
     }
 }
 
+struct LnCall {
+  const float* part; int nsplit, ldp;
+  const void *bias, *res; int ldr;
+  const void *gamma, *beta; void* out; int ldo;
+  float* out_f32; int M, n; float eps;
+  LnStage2 s2; AanFuse aan; RaggedRows rag;
+  hipStream_t stream;
+};
+template <typename T, bool WAVE, bool RAGGED, int NS, int NS2> static hipError_t ln_launch(const LnCall& a) {
+  const dim3 grid(a.M), block(WAVE ? 64 : 64 * ((a.n / 4 + 63) / 64));
+  if constexpr (WAVE)
+    hipLaunchKernelGGL((ln_wave_kernel<T, 2, RAGGED, NS, NS2>), grid, block, 0, a.stream, a.part, a.nsplit, a.ldp, (const T*)a.bias,
+                       (const T*)a.res, a.ldr, (const T*)a.gamma, (const T*)a.beta, (T*)a.out, a.ldo, a.out_f32, a.M, a.n, a.eps,
+                       a.s2, a.aan, a.rag);
+  else
+    hipLaunchKernelGGL((ln_reduce_kernel<T, RAGGED, NS, NS2>), grid, block, 0, a.stream, a.part, a.nsplit, a.ldp, (const T*)a.bias,
+                       (const T*)a.res, a.ldr, (const T*)a.gamma, (const T*)a.beta, (T*)a.out, a.ldo, a.out_f32, a.M, a.n, a.eps,
+                       a.s2, a.aan, a.rag);
+  return hipGetLastError();
+}
+// The splits that the products in front come with have kernels of their own; others, and ragged rows, take the one for
+// any number.
+template <typename T, bool WAVE> static hipError_t ln_dispatch(const LnCall& a) {
+  if (a.rag.m_dev) return ln_launch<T, WAVE, true, 0, -1>(a);
+  if (!a.s2.part) {
+    switch (a.nsplit) {
+      case 1: return ln_launch<T, WAVE, false, 1, -1>(a);
+      case 2: return ln_launch<T, WAVE, false, 2, -1>(a);
+      case 4: return ln_launch<T, WAVE, false, 4, -1>(a);
+      case 8: return ln_launch<T, WAVE, false, 8, -1>(a);
+      case 16: return ln_launch<T, WAVE, false, 16, -1>(a);
+      default: return ln_launch<T, WAVE, false, 0, -1>(a);
+    }
+  }
+  const int both = a.nsplit >= 1 && a.nsplit <= 8 && a.s2.nsplit >= 1 && a.s2.nsplit <= 8 ? 10 * a.nsplit + a.s2.nsplit : 0;
+  switch (both) {
+    case 11: return ln_launch<T, WAVE, false, 1, 1>(a);
+    case 21: return ln_launch<T, WAVE, false, 2, 1>(a);
+    case 22: return ln_launch<T, WAVE, false, 2, 2>(a);
+    case 41: return ln_launch<T, WAVE, false, 4, 1>(a);
+    case 42: return ln_launch<T, WAVE, false, 4, 2>(a);
+    case 44: return ln_launch<T, WAVE, false, 4, 4>(a);
+    case 82: return ln_launch<T, WAVE, false, 8, 2>(a);
+    case 84: return ln_launch<T, WAVE, false, 8, 4>(a);
+    case 88: return ln_launch<T, WAVE, false, 8, 8>(a);
+    default: return ln_launch<T, WAVE, false, 0, 0>(a);
+  }
+}
+
 hipError_t launch_ln_reduce(int dtype, const float* part, int nsplit, int ldp, const void* bias, const void* res, int ldr,
                             const void* gamma, const void* beta, void* out, int ldo, float* out_f32, int M, int n,
                             float eps, hipStream_t stream, const LnStage2* stage2, const AanFuse* aan, const RaggedRows* ragged) {
   if (M <= 0) return hipSuccess;
   if (n <= 0 || n > kLnMaxWaves * 256 || n % 4) return hipErrorInvalidValue;
-  LnStage2 s2{};
-  if (stage2) s2 = *stage2;
-  AanFuse af{};
-  if (aan) af = *aan;
-  RaggedRows rag{};
-  if (ragged) rag = *ragged;
-  dim3 grid(M), block(64 * ((n / 4 + 63) / 64));
+  LnCall a{part, nsplit, ldp, bias, res, ldr, gamma, beta, out, ldo, out_f32, M, n, eps, LnStage2{}, AanFuse{}, RaggedRows{}, stream};
+  if (stage2) a.s2 = *stage2;
+  if (aan) a.aan = *aan;
+  if (ragged) a.rag = *ragged;
+  if (a.rag.m_dev && a.s2.part) return hipErrorInvalidValue;   // the encoder has one stage
   auto one_of = [](int k) { return k == 1 || k == 2 || k == 4 || k == 8 || k == 16; };
-  if (n <= kLnWaveCols && one_of(nsplit) && (!s2.part || one_of(s2.nsplit))) {
-#define SAN_LN(T, RAGGED)                                                                                              \
-  hipLaunchKernelGGL((ln_wave_kernel<T, 2, RAGGED>), grid, dim3(64), 0, stream, part, nsplit, ldp, (const T*)bias,      \
-                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, rag)
-    if (dtype == 1) {
-      if (rag.m_dev) SAN_LN(bf16_t, true);
-      else SAN_LN(bf16_t, false);
-    } else {
-      if (rag.m_dev) SAN_LN(float, true);
-      else SAN_LN(float, false);
-    }
-#undef SAN_LN
-    return hipGetLastError();
-  }
-#define SAN_LN(T, RAGGED)                                                                                              \
-  hipLaunchKernelGGL((ln_reduce_kernel<T, RAGGED>), grid, block, 0, stream, part, nsplit, ldp, (const T*)bias,         \
-                     (const T*)res, ldr, (const T*)gamma, (const T*)beta, (T*)out, ldo, out_f32, M, n, eps, s2, af, rag)
-  if (dtype == 1) {
-    if (rag.m_dev) SAN_LN(bf16_t, true);
-    else SAN_LN(bf16_t, false);
-  } else {
-    if (rag.m_dev) SAN_LN(float, true);
-    else SAN_LN(float, false);
-  }
-#undef SAN_LN
-  return hipGetLastError();
+  if (n <= kLnWaveCols && one_of(nsplit) && (!a.s2.part || one_of(a.s2.nsplit)))
+    return dtype == 1 ? ln_dispatch<bf16_t, true>(a) : ln_dispatch<float, true>(a);
+  return dtype == 1 ? ln_dispatch<bf16_t, false>(a) : ln_dispatch<float, false>(a);
 }
 
 // -------------------------------------------------------------- step bookkeeping

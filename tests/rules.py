@@ -10,6 +10,7 @@ _WRAPPER = """
 #include "rules.h"
 extern "C" int split_wm(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).wm; }
 extern "C" int split_ks(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).ks; }
+extern "C" int pick_ksplit(int M, int N, int K, int dtype) { return san::gemm_pick_ksplit(M, N, K, dtype, false); }
 """
 _lib = None
 

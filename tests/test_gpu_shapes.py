@@ -70,6 +70,27 @@ def test_few_rows_match_oracle(case, loop):
     ls.gpu.close()
 
 
+# The two LayerNorms of an Eq. 5 follower in one launch, each with the k split of the product in front of it: a kernel for
+# every pair that the products come with, one for the others (16, 4), by one wave (d <= 512) and by several.
+@pytest.mark.parametrize("dtype,d,rows,block,splits", [
+    ("f32", 64, 17, 2, (1, 1)), ("f32", 128, 17, 2, (2, 2)), ("f32", 256, 17, 2, (4, 4)), ("f32", 512, 17, 2, (8, 8)),
+    ("f32", 512, 72, 4, (8, 4)), ("f32", 512, 130, 6, (8, 2)), ("f32", 512, 520, 4, (4, 1)), ("f32", 256, 520, 4, (4, 2)),
+    ("bf16", 256, 520, 4, (2, 1)), ("bf16", 512, 17, 2, (4, 4)), ("f32", 576, 17, 2, (8, 8)), ("f32", 768, 17, 6, (8, 4)),
+    ("bf16", 640, 17, 2, (4, 4)), ("bf16", 768, 72, 6, (4, 2)), ("f32", 1024, 72, 4, (8, 2)), ("f32", 1024, 17, 4, (16, 4))])
+def test_layer_norms_over_split_products(dtype, d, rows, block, splits):
+    dt = 1 if dtype == "bf16" else 0
+    assert (rules.lib().pick_ksplit(rows, d, d, dt), rules.lib().pick_ksplit(rows, block * d, d, dt)) == splits
+    cfg = _cfg(dtype=dtype, d=d, H=d // 64, F=64, V=260, batch=rows, n_dec=block, self_pi=[block], encdec_pi=[block], steps=2)
+    w = wl.make_weights(cfg, seed=8, sharp=4.0)
+    src, lens = wl.make_source(cfg, 8)
+    gpu = hz.make_gpu(cfg, w)
+    ls = hz.Lockstep(gpu, hz.make_oracle(cfg, w), src, lens, 1, subset=np.array([0, rows // 2, rows - 1]))
+    for _ in range(cfg["steps"]):
+        ls.step(logit_tol=_tol(cfg))
+    assert max(ls.log["logit_err"]) <= _tol(cfg), max(ls.log["logit_err"])
+    gpu.close()
+
+
 # a wide vocabulary whose last column tile has 4 live columns, k = 192 (an odd number of chunk pairs) and 256; wm: tiles
 # of 64 wm rows (100 rows of 128, 185 of 192, 256 two full tiles of 128, 300 two of 192, the second ragged).
 # debug = 2: the fp32 instructions instead.
