@@ -397,7 +397,7 @@ static int cand_pick_tile(int M, int N, int K, int dtype) {
   return gemm_pick_tile(M, N, K, dtype, false);
 }
 int gemm_cand_tile_n(int M, int N, int K, int dtype) {
-  if (M <= kSkinnyRows) return gemm_skinny_cand_n(N);
+  if (gemm_skinny_faster(dtype, M, N, K, 3, 1)) return gemm_skinny_cand_n(N);
   const int tile = cand_pick_tile(M, N, K, dtype);
   if (tile == 2) return 256;
   if (tile == 1 || tile == 3) return 128;
@@ -433,7 +433,7 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
   const bool wide = dtype == 1 && p.K % 128 == 0;
   const int epc = dtype == 1 ? 64 : 32;
   if (p.K <= 0 || p.K % epc != 0 || p.ksplit < 1) return hipErrorInvalidValue;
-  if (p.M <= kSkinnyRows) return launch_gemm_skinny(dtype, p, LnInput{}, stream);
+  if (gemm_skinny_faster(dtype, p.M, p.N, p.K, p.out_kind, p.ksplit)) return launch_gemm_skinny(dtype, p, LnInput{}, stream);
   if (p.ksplit > 1 && p.out_kind != 2) return hipErrorInvalidValue;   // only partial outputs may be split across blocks
   if (p.out_kind == 3) return launch_gemm_cand(dtype, p, plain, stream);
   if (dtype == 0 && !plain) {

@@ -6,10 +6,12 @@
 // waves; a wave requests all its weights (up to 16 loads of 16 bytes a lane) before anything else, straight into the
 // registers that feed the 16-row MFMA, with no LDS stage, and the eight partial tiles meet in LDS once, in wave order.
 // NV > 0: the rows are the LayerNorm of a preceding product (split-K partials + bias + residual, one or two stages as
-// in ln_reduce_kernel).  Every block normalises them itself while its weights travel -- at most 16 rows, a few KB --
-// so the LayerNorm costs no launch of its own; block 0 also stores them, as the residual of the next sub-layer.
-// Measured (one sentence, beam 4, 4 rows; us per decoder step): fp32, 6 layers of 512: 287 -> 234; bf16, 6 layers of
-// 1024: 262 -> 245.  Per launch (kernel trace): the product alone 5.4 where the tile kernel took 7.2-8.1, with its
+// in ln_reduce_kernel).  Every block normalises them itself while its weights travel, so the LayerNorm costs no launch of
+// its own; block 0 also stores them, as the residual of the next sub-layer.  Every block reads all their partials (4 rows
+// of 512 columns in four splits: 40 KB; 12 rows 120 KB), each wave its share of the rows one after the other, so this
+// pays for few and narrow rows only: few_rows_faster.
+// Measured (one sentence, beam 4, 4 rows; us per decoder step): fp32, 6 layers of 512: 276 -> 223; bf16, 6 layers of
+// 1024: 245 -> 231.  Per launch (kernel trace): the product alone 5.4 where the tile kernel took 7.2-8.1, with its
 // LayerNorm 6.1-7.5 against 3.8 + 7.5; what is left is launch, argument fetch, one trip to the Infinity Cache for the
 // weights, the reduction through LDS.  (Prologue in the output layer too: 20.5 against 17.4 + 3.2, its blocks want the
 // registers for weights; at 1024 columns it then spilled and took 44.)
@@ -242,10 +244,6 @@ __global__ __launch_bounds__(kSkWaves * 64) void skinny_kernel(GemmParams p, LnI
   }
   if (p.bump && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *p.bump = *p.bump + 1;
 }
-
-// Columns per block: 16, except in the output layer.  128 there where that still is a block per CU (every weight of
-// the layer is then requested at once); 64 below, as the candidate epilogue works on 64 columns or more.
-int gemm_skinny_cand_n(int N) { return N >= 16384 ? 128 : 64; }
 
 template <typename T, int NB, int NV, bool S2, bool CAND>
 static hipError_t launch_one(const GemmParams& p, const LnInput& ln, hipStream_t stream) {

@@ -72,7 +72,6 @@ struct LnInput {
   void* x_out;
   LnStage2 s2;
 };
-int gemm_skinny_cand_n(int N);   // column tile of out_kind 3 on this route
 hipError_t launch_gemm_skinny(int dtype, const GemmParams& p, const LnInput& ln, hipStream_t stream);
 
 // ------------------------------------------------------------------ attention

@@ -47,6 +47,41 @@ inline int gemm_skinny_ksplit(int N, int K, int dtype) {
   while (ks < 4 && tiles * ks < 128 && units % (ks * 2) == 0 && units / (ks * 2) >= 2 * 8) ks *= 2;
   return ks;
 }
+// Columns per block of its candidate form: 128 halve the slots that the beam step reads, 64 give twice the blocks.
+// Steps of 4 rows, beam 4, fp32 512 / 256 columns (us, 64 / 128): 16384 words 216 / 219, 202 / 205, 20000 words 222 / 221,
+// 206 / 204, 32000 words 224 / 223, 213 / 211.
+constexpr int kSkinnyCandWide = 18432;
+inline int gemm_skinny_cand_n(int N) { return N >= kSkinnyCandWide ? 128 : 64; }
+
+// Whether it is the faster kernel for a product of its own (us, the tile kernels / this one; weights from the Infinity
+// Cache; kind: GemmParams::out_kind).
+//   candidates: fp32 always (8000 x 512 18 / 9.5, 32000 x 512 28 / 18, 32000 x 256 19 / 14), bf16 below the line above
+//     (16000 x 512 11.6 / 8.5; 32000 x 512 12.1 / 13.4)
+//   k split over blocks: never, the tile kernels split further (512 x 512 4.1 / 5.0, bf16 3.5 / 4.4, 1024 x 4096 8.1 / 9.1)
+//   others, fp32: from k = 512 on (2048 x 512 6.9 / 5.5 at 4 rows, 7.0 / 6.3 at 16; 3072 x 1024 9.9 / 6.2; 1024 x 256
+//     4.9 / 5.1), where a block's 16 columns are enough of them (16000 x 512 12.6 / 14.1; with 128 columns, from 16384
+//     words on, 32000 x 512 21.6 / 16.5)
+//   others, bf16: from k = 1024 on and up to 6 rows (3072 x 1024 5.4 / 5.2 at 4 rows, 5.5 / 5.6 at 8; 2048 x 512 4.8 / 5.0),
+//     up to 16 where k = 2048 meets few columns (512 x 2048 7.2 / 4.9 at 4 rows, 7.4 / 5.9 at 16)
+inline bool gemm_skinny_faster(int dtype, int M, int N, int K, int kind, int ksplit) {
+  if (M > kSkinnyRows) return false;
+  if (kind == 3) return dtype == 0 || N < kSkinnyCandWide;
+  if (ksplit > 1) return false;
+  if (dtype == 0) return K >= 512 && (N <= 8 * K || (kind == 1 && N >= 16384));
+  return K >= 1024 && N <= 8 * K && (M <= 6 || (K >= 2048 && N <= 2048));
+}
+
+// Whether a cached step of `rows` rows runs with the LayerNorms inside its projections (decode_few_rows): what the
+// launches cost against what every block pays for normalising all rows itself.  A step in us, the general route / this
+// one, on both sides of each line: fp32, 64 columns 1 row 67 / 68; 128: 4 rows 135 / 133, 6 136.5 / 137; 256: 8 225 / 223,
+// 12 227 / 236; 384: 12 257 / 244, 16 258 / 258; 512: 12 253 / 252, 16 257 / 264; 768: 1 288 / 275, 6 297 / 311;
+// 1024: 1 332 / 337.  bf16, 256: 4 188 / 184, 6 187 / 193; 512: 4 211 / 201, 8 213 / 215; 768: 4 229 / 222, 6 229 / 231;
+// 1024: 4 237 / 231, 6 238 / 241, 16 251 / 294.
+inline bool few_rows_faster(int dtype, int rows, int d) {
+  if (d < 128 || d > kSkinnyLnWidth) return false;
+  if (dtype == 0) return rows <= (d < 256 ? 4 : d < 384 ? 8 : d <= 512 ? 12 : d <= 768 ? 4 : 0);
+  return rows <= (d == 512 ? 6 : 4);
+}
 
 // Tile choice: 0 = 64x64 or smaller (2x2 waves and the k-group shapes below);
 // 1 = 128x128 once that still gives ~one block per CU (the output layer);
@@ -71,7 +106,6 @@ inline int gemm_pick_tile(int M, int N, int K, int dtype, bool can_split) {
 // split factor that fills the chip for an M x N x K product (1 when the tiles alone already do)
 // plain: fp32 without splitting into bf16 parts
 inline int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain) {
-  if (M <= kSkinnyRows) return gemm_skinny_ksplit(N, K, dtype);
   if (dtype == 0 && !plain) {
     const SplitShape sp = gemm_split_shape(M, N, K, 1, 4);
     if (sp.wm) return sp.ks;

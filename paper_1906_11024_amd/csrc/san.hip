@@ -560,7 +560,7 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
     TRY(dalloc(c, &c->ab, mrows * d * esz, false));
     TRY(dalloc(c, &c->hb, mrows * wide * esz, false));
     if (aan) TRY(dalloc(c, &c->cat, drows * 2 * d * esz, false));
-    else if (!nocache && c->d <= kSkinnyLnWidth) TRY(dalloc(c, &c->x2, (size_t)std::min(c->rows_max, kSkinnyRows) * d * esz, false));
+    else if (!nocache && few_rows_faster(c->dt, 1, c->d)) TRY(dalloc(c, &c->x2, (size_t)std::min(c->rows_max, kSkinnyRows) * d * esz, false));
     c->part_elems = mrows * (c->dt == SAN_F32 ? 4 : 2) * d;
     if (c->part_elems < (size_t)4 << 20) c->part_elems = (size_t)4 << 20;
     TRY(dalloc(c, (void**)&c->part, c->part_elems * 4, false));
@@ -907,7 +907,7 @@ static int decode_cached(san_ctx* c, const int32_t* tokens, float* logits, bool 
               0, true);
 }
 
-// A cached step of at most kSkinnyRows rows with dot-product self-attention: the same layers as decode_cached, but
+// A cached step of few rows (few_rows_faster) with dot-product self-attention: the same layers as decode_cached, but
 // every LayerNorm is taken over by the projection that reads it (launch_gemm_skinny), so that a step has 5 launches
 // for a layer that follows in both of its blocks and 8 for one that heads both, instead of 7 and 11.  The rows x live
 // in c->x and c->x2 in turn: a projection that normalises its input reads the residual from one and stores the new
@@ -950,9 +950,13 @@ static int decode_few_rows(san_ctx* c, const int32_t* tokens, float* logits, boo
   };
   // partials of A W^T (N columns)
   auto partials = [&](const void* A, const void* W, int N, int K, float* out, int ks) -> int {
-    return gemm(c, A, K, W, nullptr, B, N, K, 0, 2, out, N, 0, nullptr, 0, 0, nullptr, 0, 0, 0, false, ks);
+    GemmParams p{};
+    p.A = A; p.lda = K; p.W = W; p.out[0] = out; p.ldo[0] = N; p.seg_w = 1 << 30;
+    p.M = B; p.N = N; p.K = K; p.out_kind = 2; p.ksplit = ks;
+    LAUNCH(c, launch_gemm_skinny(c->dt, p, LnInput{}, c->stream));
+    return SAN_OK;
   };
-  const int ks_d = std::min(gemm_pick_ksplit(B, d, d, c->dt, c->plain), 2), ks_f = gemm_pick_ksplit(B, d, c->F, c->dt, c->plain);
+  const int ks_d = std::min(gemm_skinny_ksplit(d, d, c->dt), 2), ks_f = gemm_skinny_ksplit(d, c->F, c->dt);
   const int Ld = (int)c->dec.size();
   for (int n = 0; n < Ld; ++n) {
     DecLayer& L = c->dec[n];
@@ -1011,7 +1015,7 @@ static int decode_few_rows(san_ctx* c, const int32_t* tokens, float* logits, boo
     if (Hd.wo_blk) {   // Eq. 5 block: the head projects the shared context for all its layers
       ldy = Hd.blk_size * d;
       if (chead) {
-        int ks = std::min(gemm_pick_ksplit(B, ldy, d, c->dt, c->plain), 2);
+        int ks = std::min(gemm_skinny_ksplit(ldy, d, c->dt), 2);
         while (ks > 1 && (size_t)ks * B * ldy > Hd.y_elems) ks /= 2;
         Hd.y_ks = ks;
         if ((rc = partials(A, Hd.wo_blk, ldy, d, Hd.y_blk, ks))) return rc;
@@ -1148,7 +1152,7 @@ static int decode_step_impl(san_ctx* c, const int32_t* tokens_dev, float* logits
   c->launches = 0;
   // few rows: fewer, smaller launches.  cfg.debug keeps the general route: its per-layer copies are written by the
   // LayerNorm launches, and it is the cross-check of the other one
-  const bool few = c->batch * c->cfg.beam <= kSkinnyRows && c->x2 && !c->cfg.debug;
+  const bool few = c->x2 && few_rows_faster(c->dt, c->batch * c->cfg.beam, c->d) && !c->cfg.debug;
   int rc = !c->cfg.use_cache ? decode_uncached(c, tokens_dev, logits_dev)
            : few             ? decode_few_rows(c, tokens_dev, logits_dev, skip_embed)
                              : decode_cached(c, tokens_dev, logits_dev, skip_embed);

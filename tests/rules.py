@@ -10,6 +10,9 @@ _WRAPPER = """
 #include "rules.h"
 extern "C" int split_wm(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).wm; }
 extern "C" int split_ks(int M, int N, int K, int ks_min, int ks_max) { return san::gemm_split_shape(M, N, K, ks_min, ks_max).ks; }
+extern "C" int few_rows(int dtype, int rows, int d) { return san::few_rows_faster(dtype, rows, d); }
+extern "C" int skinny(int dtype, int M, int N, int K, int kind, int ks) { return san::gemm_skinny_faster(dtype, M, N, K, kind, ks); }
+extern "C" int cand_n(int N) { return san::gemm_skinny_cand_n(N); }
 extern "C" int pick_ksplit(int M, int N, int K, int dtype) { return san::gemm_pick_ksplit(M, N, K, dtype, false); }
 """
 _lib = None

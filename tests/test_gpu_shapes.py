@@ -42,18 +42,18 @@ _FEW = {
     # one row; fewer 64-byte units of k (4, bf16: 2) than the eight waves that share them; ragged vocabulary
     "one_row": dict(),
     "one_row_bf16": dict(dtype="bf16", F=64),
-    # the last row count of the route, and the first beyond it
+    # the last row count of the products of few rows, and the first beyond it
     "rows16": dict(batch=4, beam=4, d=512, H=8, F=1024, V=16388),
     "rows17": dict(batch=17, d=512, H=8, F=1024, V=16388),
     # general route, LayerNorm rows that leave lanes of their one wave idle
     "rows20_d320": dict(batch=5, beam=4, d=320, H=5, F=192),
     "rows20_d320_bf16": dict(dtype="bf16", batch=5, beam=4, d=320, H=5, F=192),
-    # rows not a multiple of a wave's share, a width that leaves lanes of the LayerNorm idle, k splits that are odd
+    # widths and row counts around the steps of the kernel's shares
     "rows15_d576_share_s": dict(batch=3, beam=5, d=576, H=9, F=832, share="S"),
     "rows9_d1024": dict(batch=3, beam=3, d=1024, H=16, F=1088, self_pi=[1, 2], encdec_pi=[3]),
     "rows16_d1024_bf16": dict(dtype="bf16", batch=2, beam=8, d=1024, H=16, F=4096, V=16388),
     "rows6_d832_bf16_share_s": dict(dtype="bf16", batch=3, beam=2, d=832, H=13, F=320, share="S", encdec_pi=[3]),
-    # wider than the LayerNorm inside the projection takes
+    # wider than any projection with a LayerNorm inside
     "rows4_d1088": dict(batch=2, beam=2, d=1088, H=17, F=256),
     "rows12_aan": dict(batch=3, beam=4, self_kind="aan", self_pi=[1, 1, 1]),
 }
@@ -65,6 +65,30 @@ def test_few_rows_match_oracle(case, loop):
     cfg = _cfg(**_FEW[case])
     share = cfg.pop("share", "A")
     ls = _lockstep(cfg, share, loop)
+    if loop is None:
+        assert max(ls.log["logit_err"]) <= _tol(cfg), max(ls.log["logit_err"])
+    ls.gpu.close()
+
+
+# Steps with the LayerNorms inside the projections, at the last row count of each width that takes them (few = 1), and at
+# the next, which runs the general launches with products of few rows where those are faster: both kinds of block, one
+# LayerNorm or two per projection, split weights shared or not, vocabularies on both sides of the output layer's lines.
+@pytest.mark.parametrize("loop", [None, "cands"])
+@pytest.mark.parametrize("dtype,d,batch,beam,few,kw", [
+    ("f32", 64, 1, 1, 0, {}), ("f32", 128, 1, 4, 1, {}), ("f32", 128, 5, 1, 0, {}), ("f32", 256, 2, 4, 1, dict(V=18436)),
+    ("f32", 256, 3, 3, 0, dict(V=18428)), ("f32", 512, 3, 4, 1, dict(F=1088, V=18436)), ("f32", 512, 13, 1, 0, dict(F=1088, V=16388)),
+    ("f32", 576, 2, 2, 1, dict(share="S")), ("f32", 768, 4, 1, 1, dict(F=2048, encdec_pi=[3])), ("f32", 768, 5, 1, 0, dict(F=3072)),
+    ("f32", 1024, 1, 1, 0, dict(F=2048)), ("bf16", 256, 1, 4, 1, dict(V=18428)), ("bf16", 512, 2, 3, 1, dict(F=2048, V=18436)),
+    ("bf16", 512, 7, 1, 0, dict(F=2048)), ("bf16", 1024, 1, 4, 1, dict(F=4096, self_pi=[1, 2], encdec_pi=[3])),
+    ("bf16", 832, 2, 2, 1, dict(share="S")), ("bf16", 1024, 5, 1, 0, dict(F=4096)),
+    ("bf16", 512, 3, 4, 0, dict(F=2048, self_kind="aan", self_pi=[1, 1, 1]))])
+def test_few_rows_on_both_sides_of_the_rule(dtype, d, batch, beam, few, kw, loop):
+    L, dt, rows = rules.lib(), 1 if dtype == "bf16" else 0, batch * beam
+    if kw.get("self_kind") != "aan":
+        assert L.few_rows(dt, rows, d) == few
+    cfg = _cfg(dtype=dtype, d=d, H=d // 64, F=kw.get("F", 320), batch=batch, beam=beam, steps=3)
+    cfg.update({k: v for k, v in kw.items() if k != "share"})
+    ls = _lockstep(cfg, kw.get("share", "A"), loop)
     if loop is None:
         assert max(ls.log["logit_err"]) <= _tol(cfg), max(ls.log["logit_err"])
     ls.gpu.close()
