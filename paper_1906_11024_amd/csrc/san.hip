@@ -138,7 +138,7 @@ struct san_ctx {
   int batch_enc = 0;           // sentences given to san_encode
   int* src_len0 = nullptr;     // their lengths (src_len holds those of the current batch)
   int* group_map = nullptr;    // [max_batch] encode-time index of each current sentence
-  void* enc_packed = nullptr;  // bf16, 64-wide heads: keys and values of one encoder layer in MFMA fragment order
+  void* enc_packed = nullptr;  // bf16, 64-wide heads: keys and values of one encoder layer in MFMA fragment order (in hb)
   int* enc_off = nullptr;      // [max_batch + 1] first row of each sentence while the encoder runs without padding
   int* enc_slot = nullptr;     // [max_batch * max_src_len] their padded rows in that order (launch_embed)
   const int* m_dev = nullptr;  // set while it does: the number of rows (enc_off[batch]); null otherwise
@@ -558,10 +558,16 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
     TRY(dalloc(c, &c->x, mrows * d * esz, false));
     TRY(dalloc(c, &c->qkv, mrows * 3 * d * esz, false));
     TRY(dalloc(c, &c->ab, mrows * d * esz, false));
-    TRY(dalloc(c, &c->hb, mrows * wide * esz, false));
+    // the encoder's keys and values in fragment order lie in hb: an attention layer is done with them before its
+    // feed-forward layer begins
+    const bool enc_mfma = c->dt == SAN_BF16 && c->dh == 64 && !cfg->debug && c->rows_src_max >= kEncMfmaMinRows;
+    const size_t packed = enc_mfma ? (size_t)cfg->max_batch * c->H * (c->src_pad / 32) * 8192 : 0;
+    TRY(dalloc(c, &c->hb, std::max(mrows * wide * esz, packed), false));
+    if (enc_mfma) c->enc_packed = c->hb;
     if (aan) TRY(dalloc(c, &c->cat, drows * 2 * d * esz, false));
     else if (!nocache && few_rows_faster(c->dt, 1, c->d)) TRY(dalloc(c, &c->x2, (size_t)std::min(c->rows_max, kSkinnyRows) * d * esz, false));
-    c->part_elems = mrows * (c->dt == SAN_F32 ? 4 : 2) * d;
+    // split-K partials: two splits of any product, four of the encoder's large fp32 ones (gemm_split_shape)
+    c->part_elems = std::max(mrows * 2, (size_t)c->rows_src_max * (c->dt == SAN_F32 ? 4 : 2)) * d;
     if (c->part_elems < (size_t)4 << 20) c->part_elems = (size_t)4 << 20;
     TRY(dalloc(c, (void**)&c->part, c->part_elems * 4, false));
     TRY(dalloc(c, (void**)&c->t_dev, 256, false));
@@ -577,8 +583,6 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
     TRY(dalloc(c, (void**)&c->keep_dev, (size_t)cfg->max_batch * 4, false));
     TRY(dalloc(c, (void**)&c->enc_off, ((size_t)cfg->max_batch + 1) * 4, false));
     if (c->rows_src_max >= kRaggedMinRows) TRY(dalloc(c, (void**)&c->enc_slot, (size_t)c->rows_src_max * 4, false));
-    if (c->dt == SAN_BF16 && c->dh == 64 && !cfg->debug && c->rows_src_max >= kEncMfmaMinRows)
-      TRY(dalloc(c, &c->enc_packed, (size_t)cfg->max_batch * c->H * (c->src_pad / 32) * 8192, false));
     {
       std::vector<int> iota((size_t)c->rows_max);
       for (size_t i = 0; i < iota.size(); ++i) iota[i] = (int)i;

@@ -261,6 +261,27 @@ def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_
     gpu.close()
 
 
+def test_state_of_a_context_holds_no_encoder_scratch():
+    """What the matrix-core kernels add to a bf16 context is the fragment-ordered memory of each enc-dec head (debug = 2
+    keeps neither it nor the encoder's copy); what caching saves is not given back in partials."""
+    cfg = _cfg(n_enc=1, n_dec=2, d=128, H=2, F=512, dtype="bf16", batch=40, src_len=(64, 64), self_pi=[2], encdec_pi=[1, 1])
+    w = wl.make_weights(cfg, seed=2)
+    size = {}
+    for debug in (0, 2):
+        gpu = hz.make_gpu(cfg, w, debug=debug)
+        size[debug] = gpu.device_bytes(1)
+        gpu.close()
+    packed = 40 * 2 * (64 // 32) * 8192                     # sentences, heads, blocks of 32 positions
+    assert size[0] - size[2] == 2 * packed
+    cfg = _cfg(d=512, H=8, F=64, batch=64, src_len=(4, 4), steps=64, n_dec=1, self_pi=[1], encdec_pi=[1])
+    gpu = hz.make_gpu(cfg, wl.make_weights(cfg, seed=2), use_cache=0)
+    rows = 64 * 64
+    # x, q k v, attention output, hidden rows (2 d at least), two partials, and less than a quarter of that for the rest
+    # (scores: heads x (positions + source) per row)
+    assert gpu.device_bytes(1) <= 1.25 * rows * 512 * 4 * (1 + 3 + 1 + 2 + 2 + 1) + rows * 8 * (64 + 4) * 4
+    gpu.close()
+
+
 @pytest.mark.parametrize("batch,max_src,lens,enc_pi", [(9, 140, (0, 1, 31, 32, 33, 63, 65, 129, 140), None),   # five key blocks: the loop
                                                        (16, 32, None, None),                       # one block, all sentences full
                                                        (9, 70, (70, 64, 33, 32, 1, 0, 69, 70, 5), [2, 1])])   # weights emitted
