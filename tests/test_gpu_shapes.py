@@ -344,3 +344,31 @@ def _check_picks(V, beam, k):
         assert np.array_equal(o_tok[b].cpu().numpy(), flat % V), b
         assert np.array_equal(o_par[b].cpu().numpy(), b * beam + flat // V), b
     gpu.close()
+
+
+@pytest.mark.parametrize("beam,steps,dtype", [(20, 70, "f32"), (32, 70, "f32"), (12, 129, "bf16"), (17, 66, "f32")])
+def test_wide_beam_tail_permutes_long_histories(beam, steps, dtype):
+    """san_decode_n with more than 64 past positions (the tail permutes 64 columns of the ancestry table at a time, the last
+    pass ragged) against the three separate calls: the same words and parents at every step, the same scores."""
+    V, batch = 212, 2
+    cfg = _cfg(dtype=dtype, batch=batch, beam=beam, V=V, steps=steps, n_dec=2, self_pi=[1, 1], encdec_pi=[1, 1])
+    w = wl.make_weights(cfg, seed=12, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(8.0)
+    if dtype == "bf16":
+        w["w_out"] = wl.round_to_bf16(w["w_out"])
+    src, lens = wl.make_source(cfg, 12)
+    gpu = hz.make_gpu(cfg, w)
+    ref = hz.gpu_free_run(gpu, src, lens, beam, steps)
+    gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+    rows = batch * beam
+    cum = torch.full((rows,), -np.inf, device="cuda")
+    cum[::beam] = 0.0
+    tok, par = (torch.zeros((steps, rows), dtype=torch.int32, device="cuda") for _ in range(2))
+    gpu.decode_n(steps, torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda"), cum, tok, par,
+                 torch.empty((rows, V), device="cuda"), keep_logits=True)
+    assert np.array_equal(tok.cpu().numpy(), np.stack(ref["tokens"]))
+    assert np.array_equal(par.cpu().numpy(), np.stack(ref["parents"]))
+    assert np.array_equal(cum.cpu().numpy(), ref["scores"][-1].reshape(-1))
+    moved = np.stack(ref["parents"])[64:] != np.arange(rows)
+    assert moved.any()                                       # the permutation has something to do past 64 columns
+    gpu.close()
