@@ -38,7 +38,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
+# Highest rate of a product on the matrix cores, by model type.  fp32: large products are eight bf16 products of the
+# operands' parts each (2500 / 8); the fp32 instructions, which small products use, reach 157.3.
+MFMA_PEAK_TFLOPS = {"f32": 312.5, "bf16": 2500.0}
 
 
 def parse():

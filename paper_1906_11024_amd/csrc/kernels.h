@@ -61,8 +61,9 @@ struct LnStage2 {
   const void *bias, *gamma, *beta;
 };
 
-// The same product for at most kSkinnyRows rows (gemm_skinny.hip).  launch_gemm takes this route by itself; called
-// directly it can also build its rows first: with ln.part set, A is ignored and row m is
+// The same product for at most kSkinnyRows rows (gemm_skinny.hip).  launch_gemm takes this route where
+// gemm_skinny_faster says so; called directly it can also build its rows first: with ln.part set, A is ignored and
+// row m is
 //   x[m] = LayerNorm(sum_s part[s][m] + bias + res[m]) * gamma + beta   (then stage 2, if given), width K,
 // which block 0 stores to x_out (optional; not the buffer res).
 struct LnInput {

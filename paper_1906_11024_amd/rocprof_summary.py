@@ -11,7 +11,7 @@ under profiles/.
       copy kernel of known size that bench.py --calib-copy-mb adds to the run
 
   python -m paper_1906_11024_amd.rocprof_summary mfma <counter_collection.csv> --dtype f32 [--trace <results.db>]
-      matrix-core use of every GEMM shape: SQ_VALU_MFMA_BUSY_CYCLES (summed over the SIMDs)
+      matrix-core use of every shape of gemm_kernel (not of the split products): SQ_VALU_MFMA_BUSY_CYCLES (summed over the SIMDs)
       against GRBM_GUI_ACTIVE x 1024 SIMDs, and the flops the MFMA op counter saw
       (SQ_INSTS_VALU_MFMA_MOPS_* x 512) against the algorithmic 2 M N K where the shape is known
 
