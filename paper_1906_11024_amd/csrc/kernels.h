@@ -232,6 +232,36 @@ hipError_t launch_reorder_table(int* tab, int ld, const int* parent, const int* 
 hipError_t launch_reorder_rows(float* st, size_t layer_stride, const int* parent, int layers, int batch, int beam,
                                int d, hipStream_t stream);
 
+// ---------------------------------------------------------------- small models
+// Decoder steps of a small fp32 model with dot-product self-attention (small_model.hip): one workgroup per sentence runs
+// `steps` whole steps, the beam search included, without another launch.
+struct SmallLayer {            // device array, one per decoder layer
+  int self_head, ctx_head;     // this layer heads its blocks
+  int ctx_ld;                  // elements between two positions of its encoder memory: 2 d (head), d (follower with values of its own), 0
+  const float *w_self, *b_self, *wo, *bo, *ln1g, *ln1b;                 // [3d][d] (q;k;v) or [d][d] (v)
+  const float *wq_c, *bq_c, *wo_c, *bo_c, *ln2g, *ln2b;
+  const float *w1, *b1, *w2, *b2, *ln3g, *ln3b;
+  float *Kc, *Vc;              // [position][cache_rows][d]
+  float *S_self, *S_ctx;       // weights a head writes for its followers (null: none), a follower reads
+  const float *mem_k, *mem_v;
+};
+struct SmallDecode {
+  const SmallLayer* layers; int n_layers;
+  int d, F, H, V, beam, T, max_src, max_src_cap, cache_rows;   // T: capacity of a hypothesis; max_src: positions per memory slot
+  const float *emb, *pe, *w_out; float emb_scale, scale, eps;
+  int *t_dev, *ticket;         // steps done (read by every workgroup, moved by the last one to end); 0
+  int *anc, *last_tok; const int *src_len, *group_map;
+  int steps;
+  const int* tok_in;           // words fed first
+  float* logits;               // not null: one step, its logits, no search (nothing below is used)
+  const float* cum_in; float* cum_out; int* tok_out;             // scores before and after, words picked last
+  int *out_tok, *out_par; int step0, out_ld; const int* row_map; // picks of step s at [step0 + s][out_ld]; row_map: see TopkHistory
+  int eos; int *done, *done_count;
+  int feed_last;               // the picks of the last step count as fed (the loop's next step needs no embedding)
+};
+size_t small_decode_lds(const SmallDecode& p);   // LDS bytes of a workgroup
+hipError_t launch_small_decode(const SmallDecode& p, int batch, hipStream_t stream);
+
 // ------------------------------------------------------------- policy learning
 constexpr int kMaxPolicyLayers = 32;
 struct JsParams {

@@ -83,6 +83,22 @@ inline bool few_rows_faster(int dtype, int rows, int d) {
   return rows <= (d == 512 ? 6 : 4);
 }
 
+// Models whose decoder steps run with one workgroup per sentence (small_model.hip), and whether they do for `batch`
+// sentences.  A model of both routes, in us a step of R = beam rows a sentence and L layers, with MB the weights a step
+// reads, all of them by one workgroup:
+//   one workgroup a sentence   6 + 6.2 L + (5 + 4 R) MB for every 256 sentences
+//   launches                   21 + 27 L
+// Measured (us, launches / one workgroup): 64 columns, F 256, 2 layers, 1000 words (0.7 MB) beam 1 70 / 21, 4 73 / 32,
+// 8 78 / 44, 300 sentences of beam 1 79 / 42; 6 layers (1.6 MB) beam 4 182 / 76; 4000 words (1.5 MB) beam 4 74 / 48;
+// 128 columns, F 512, 2 layers, 1000 words (2.3 MB) beam 1 72 / 35, 4 77 / 59; 6 layers, 2004 words (6.5 MB) beam 1
+// 190 / 111, 4 192 / 175, 8 196 / 240.  The line leaves 15 % to the launches.
+constexpr int kSmallLds = 160 * 1024, kSmallBeam = 8;   // LDS of a workgroup; its search sorts the candidates of this beam at once
+inline bool small_model_faster(int d, int F, int V, int layers, int beam, int batch) {
+  if ((d != 64 && d != 128) || (F != 64 && F != 128 && F != 256 && F != 512) || beam < 1 || beam > kSmallBeam || batch < 1) return false;
+  const float mb = 4e-6f * ((float)layers * (6.f * d * d + 2.f * d * F) + (float)V * d);
+  return (float)((batch + 255) / 256) * (6.f + 6.2f * layers + (5.f + 4.f * beam) * mb) <= 0.85f * (21.f + 27.f * layers);
+}
+
 // Tile choice: 0 = 64x64 or smaller (2x2 waves and the k-group shapes below);
 // 1 = 128x128 once that still gives ~one block per CU (the output layer);
 // 2 = 256x256 (bf16 only) once that does; 3 = see below.  The wide output layer is bound by

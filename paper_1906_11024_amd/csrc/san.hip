@@ -112,6 +112,7 @@ struct san_ctx {
   void* x2 = nullptr;         // second residual buffer of decode_few_rows, [min(rows_max, kSkinnyRows)][d]
   float* part = nullptr;
   size_t part_elems = 0;
+  SmallLayer* small_layers = nullptr;   // models whose steps can run in one launch (small_model.hip); null: not this one
   float* aan_all = nullptr;   // AAN running sums [layer][rows_max][d]
   float* dbg_enc = nullptr;   // debug copy of the encoder output [batch*max_src][d]
   // policy learning: running JS sums [2][L][L] (self, enc-dec), per-pair scratch, sample counts
@@ -602,6 +603,30 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
       HIP_TRY(c, hipMemset(c->t_dev, 0, 256));
     }
     c->weights.clear();
+    if (c->dt == SAN_F32 && !aan && !nocache && !cfg->debug && small_model_faster(c->d, c->F, c->V, Ld, cfg->beam, 1)) {
+      std::vector<SmallLayer> sl(Ld);
+      for (int n = 0; n < Ld; ++n) {
+        const DecLayer &L = c->dec[n], &Hd = c->dec[L.ctx_head];
+        SmallLayer& o = sl[n];
+        auto f = [](void* p) { return (const float*)p; };
+        o.self_head = L.self_head == n;
+        o.ctx_head = L.ctx_head == n;
+        o.ctx_ld = o.ctx_head ? 2 * c->d : (shareS ? c->d : 0);
+        o.w_self = f(L.w_self); o.b_self = f(L.b_self); o.wo = f(L.wo); o.bo = f(L.bo); o.ln1g = f(L.ln1g); o.ln1b = f(L.ln1b);
+        o.wq_c = f(L.wq_c); o.bq_c = f(L.bq_c); o.bo_c = f(L.bo_c); o.ln2g = f(L.ln2g); o.ln2b = f(L.ln2b);
+        o.wo_c = Hd.wo_blk ? f(Hd.wo_blk) + (size_t)(n - L.ctx_head) * d * d : f(L.wo_c);
+        o.w1 = f(L.w1); o.b1 = f(L.b1); o.w2 = f(L.w2); o.b2 = f(L.b2); o.ln3g = f(L.ln3g); o.ln3b = f(L.ln3b);
+        o.Kc = (float*)L.Kc; o.Vc = (float*)L.Vc;
+        const bool self_shared = !o.self_head || (n + 1 < Ld && c->dec[n + 1].self_head == n);
+        const bool ctx_shared = shareS && (!o.ctx_head || (n + 1 < Ld && c->dec[n + 1].ctx_head == n));
+        o.S_self = self_shared ? c->dec[L.self_head].S_self : nullptr;
+        o.S_ctx = ctx_shared ? Hd.S_ctx : nullptr;
+        o.mem_k = f(L.mem);
+        o.mem_v = o.ctx_head ? f(L.mem) + d : f(L.mem);
+      }
+      TRY(dalloc(c, (void**)&c->small_layers, sizeof(SmallLayer) * Ld, false));
+      HIP_TRY(c, hipMemcpy(c->small_layers, sl.data(), sizeof(SmallLayer) * Ld, hipMemcpyHostToDevice));
+    }
     HIP_TRY(c, hipMemset(c->last_tok, 0xff, (size_t)c->rows_max * 4));
     HIP_TRY(c, hipDeviceSynchronize());
 #undef TRY
@@ -1148,12 +1173,45 @@ static int decode_uncached(san_ctx* c, const int32_t* tokens, float* logits) {
               c->V, 0, nullptr, 0, 0, nullptr, 0, 0, 0, false, 0, true);
 }
 
+// What every launch of small_model.hip's decoder shares; the caller adds the words and where the results go.
+static SmallDecode small_decode(const san_ctx* c) {
+  SmallDecode p{};
+  p.layers = c->small_layers; p.n_layers = (int)c->dec.size();
+  p.d = c->d; p.F = c->F; p.H = c->H; p.V = c->V; p.beam = c->cfg.beam; p.T = c->cfg.max_tgt_len;
+  p.max_src = c->max_src; p.max_src_cap = c->cfg.max_src_len; p.cache_rows = c->batch_enc * c->cfg.beam;
+  p.emb = (const float*)c->tgt_emb; p.pe = c->pe; p.w_out = (const float*)c->w_out;
+  p.emb_scale = (float)std::sqrt((double)c->d); p.scale = 1.0f / std::sqrt((float)c->dh); p.eps = c->cfg.ln_eps;
+  p.t_dev = c->t_dev; p.ticket = c->t_dev + 1;
+  p.anc = c->anc; p.last_tok = c->last_tok; p.src_len = c->src_len;
+  p.group_map = c->batch != c->batch_enc ? c->group_map : nullptr;
+  p.steps = 1;
+  p.eos = c->cfg.eos_id; p.done = c->done_dev; p.done_count = c->done_dev + c->cfg.max_batch;
+  return p;
+}
+// Whether steps run there (san_profile times the launches of the general route)
+static bool small_route(const san_ctx* c, bool search) {
+  if (!c->small_layers || c->prof_on ||
+      !small_model_faster(c->d, c->F, c->V, (int)c->dec.size(), c->cfg.beam, c->batch))
+    return false;
+  SmallDecode p = small_decode(c);
+  if (!search) p.logits = (float*)1;   // only whether it is there counts
+  return small_decode_lds(p) <= kSmallLds;
+}
+
 static int decode_step_impl(san_ctx* c, const int32_t* tokens_dev, float* logits_dev, bool skip_embed) {
   if (!c) return SAN_EINVAL;
   if (!tokens_dev || !logits_dev) return fail(c, SAN_EINVAL, "san_decode_step: null argument");
   if (c->t < 0) return fail(c, SAN_ESTATE, "san_decode_step before san_encode");
   if (c->t >= c->cfg.max_tgt_len) return fail(c, SAN_ECAPACITY, "san_decode_step: max_tgt_len steps already decoded");
   c->launches = 0;
+  if (!skip_embed && c->cand_tiles == 0 && small_route(c, false)) {
+    SmallDecode p = small_decode(c);
+    p.tok_in = tokens_dev;
+    p.logits = logits_dev;
+    LAUNCH(c, launch_small_decode(p, c->batch, c->stream));
+    c->t += 1;
+    return SAN_OK;
+  }
   // few rows: fewer, smaller launches.  cfg.debug keeps the general route: its per-layer copies are written by the
   // LayerNorm launches, and it is the cross-check of the other one
   const bool few = c->x2 && few_rows_faster(c->dt, c->batch * c->cfg.beam, c->d) && !c->cfg.debug;
@@ -1478,16 +1536,19 @@ int san_decode_n(san_ctx* c, int32_t n, const int32_t* tokens_dev, float* cum_io
       if ((rc = dalloc(c, (void**)&c->part_ms, slots * 2 * 4, false))) return rc;   // last: it switches the mode on
     }
   }
+  const bool small = !(flags & SAN_LOOP_LOGITS) && small_route(c, true);
+  if (!small) {
   HIP_TRY(c, hipMemcpyAsync(c->pp_tok[0], tokens_dev, (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->pp_cum[0], cum_io_dev, (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->t0_dev, c->t_dev, 4, hipMemcpyDeviceToDevice, c->stream));
+  }
   if (compact)
     HIP_TRY(c, hipMemcpyAsync(c->row_map, c->iota_dev, (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));
   // The beam step's tail is fused (see loop_step) unless finished sentences may leave the batch
   // during this call (their state is then regathered between steps) or nothing is cached.
   const bool fused = c->cfg.use_cache && !compact && c->cfg.beam <= 32;
   const int mode = (fused ? 1 : 0) | ((c->cfg.use_cache && !(flags & SAN_LOOP_LOGITS)) ? 2 : 0);
-  if (fused && c->cfg.self_kind != SAN_SELF_AAN) {
+  if (fused && !small && c->cfg.self_kind != SAN_SELF_AAN) {
     // the first step's input; every later one is embedded by the step before it
     c->kind = SAN_K_MISC;
     LAUNCH(c, launch_embed(c->dt, c->pp_tok[0], 1, 1, c->tgt_emb, c->pe, c->t_dev, c->x, rows0, c->d, c->V,
@@ -1546,6 +1607,24 @@ int san_decode_n(san_ctx* c, int32_t n, const int32_t* tokens_dev, float* cum_io
     const int rows = c->batch * beam;
     const int entry_rows = compacted ? rows0 : 0;
     int action = kGoOn;
+    if (small) {   // as many steps per launch as lie between two checks
+      if ((rc = check(action))) return rc;
+      if (action != kGoOn) continue;
+      SmallDecode p = small_decode(c);
+      p.steps = c->cfg.eos_id < 0 ? n - done : std::min(n - done, kCheckEvery - (done - last_check));
+      const int q = (done + p.steps) & 1;
+      p.tok_in = done ? c->pp_tok[done & 1] : tokens_dev;
+      p.cum_in = done ? c->pp_cum[done & 1] : cum_io_dev;
+      p.tok_out = c->pp_tok[q];
+      p.cum_out = c->cfg.eos_id < 0 ? cum_io_dev : c->pp_cum[q];   // all steps in one launch: the scores are final
+      p.out_tok = out_tokens_dev; p.out_par = out_parents_dev;
+      p.step0 = done; p.out_ld = rows0; p.row_map = compacted ? c->row_map : nullptr;
+      p.feed_last = fused;
+      LAUNCH(c, launch_small_decode(p, c->batch, c->stream));
+      c->t += p.steps;
+      done += p.steps;
+      continue;
+    }
     if (use_graph && n - done >= 2 && (done & 1) == 0) {
       // the graph holds two steps (parity 0 then 1); it is rebuilt when the caller's
       // buffers or the batch change
@@ -1595,6 +1674,7 @@ int san_decode_n(san_ctx* c, int32_t n, const int32_t* tokens_dev, float* cum_io
       ++done;
     }
   }
+  if (small && c->cfg.eos_id < 0) return SAN_OK;
   if (!compacted) {
     HIP_TRY(c, hipMemcpyAsync(cum_io_dev, c->pp_cum[done & 1], (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));
     return SAN_OK;

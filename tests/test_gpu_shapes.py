@@ -372,3 +372,74 @@ def test_wide_beam_tail_permutes_long_histories(beam, steps, dtype):
     moved = np.stack(ref["parents"])[64:] != np.arange(rows)
     assert moved.any()                                       # the permutation has something to do past 64 columns
     gpu.close()
+
+
+# Small fp32 models, one workgroup per sentence: both widths, every feed-forward width and head width, beams on both sides
+# of its row blocks and of its wave-per-part search, vocabularies that leave waves and lanes without words, histories too
+# long for sixteen lanes a head, empty sources, both kinds of enc-dec sharing.
+_SMALL = {
+    "greedy": dict(batch=3),
+    "words_fewer_than_waves": dict(V=68, batch=2, beam=2),
+    "d64_heads16_beam8": dict(F=64, beam=8, batch=2),
+    "d64_heads64_beam3": dict(H=1, F=256, beam=3, batch=2, share="S", encdec_pi=[3]),
+    "d64_f512_beam5": dict(H=2, F=512, beam=5, batch=2, self_pi=[1, 2], V=2004),
+    "d128_heads16_beam4": dict(d=128, H=8, F=128, beam=4, batch=3, src_len=(1, 40)),
+    "d128_heads128_beam2": dict(d=128, H=1, F=512, beam=2, share="S"),
+    "d128_heads32_beam6": dict(d=128, H=4, F=64, beam=6, self_pi=[3], encdec_pi=[1, 1, 1]),
+    "many_sentences": dict(batch=260, n_dec=2, self_pi=[2], encdec_pi=[2], V=260, src_len=(0, 3)),
+    "long_history": dict(beam=4, steps=262, V=260, F=64),
+}
+
+
+@pytest.mark.parametrize("loop", [None, "cands"])
+@pytest.mark.parametrize("case", sorted(_SMALL))
+def test_small_models_match_oracle(case, loop):
+    cfg = _cfg(**_SMALL[case])
+    share = cfg.pop("share", "A")
+    assert rules.lib().small_model(cfg["d"], cfg["F"], cfg["V"], cfg["n_dec"], cfg["beam"], cfg["batch"])
+    ls = _lockstep(cfg, share, loop)
+    if loop is None:
+        assert max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
+        assert ls.gpu.last_launch_count == 1
+    ls.gpu.close()
+
+
+# Several steps inside one launch, with and without end symbols, graph flag and compaction, then single steps on the state
+# they leave, against the launches (debug = 2) on the same weights.  The seed's searches have no near ties: scores differ by
+# the roundings of 32-bit sums (2e-5 of sums of up to 40 log-probabilities).
+@pytest.mark.parametrize("eos,compact,beam", [(-1, False, 4), (wl.EOS_ID, False, 4), (wl.EOS_ID, True, 4), (-1, False, 1)])
+def test_small_models_loop_equals_the_launches(eos, compact, beam):
+    cfg = _cfg(batch=6, beam=beam, steps=44, V=260, src_len=(2, 9))
+    assert rules.lib().small_model(cfg["d"], cfg["F"], cfg["V"], cfg["n_dec"], beam, cfg["batch"])
+    w = wl.make_weights(cfg, seed=5, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(20.0)
+    if eos >= 0:
+        w["w_out"][eos] *= np.float32(2.0)     # some sentences end early
+    src, lens = wl.make_source(cfg, 5)
+    rows, out = cfg["batch"] * beam, []
+    for debug in (0, 2):
+        gpu = hz.make_gpu(cfg, w, eos_id=eos, debug=debug)
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+        cum = torch.full((cfg["batch"], beam), -float("inf"), device="cuda")
+        cum[:, 0] = 0.0
+        cum = cum.reshape(-1).contiguous()
+        toks = torch.zeros(40, rows, dtype=torch.int32, device="cuda")
+        pars = torch.zeros_like(toks)
+        logits = torch.empty(rows, cfg["V"], device="cuda")
+        gpu.decode_n(21, tok, cum, toks, pars, logits, compact=compact)
+        step, active = gpu.step, gpu.active()
+        more = []
+        if len(active) == cfg["batch"] and step == 21:
+            t2, c2 = toks[20].clone(), cum.clone()
+            gpu.decode_n(3, t2, c2, toks[21:], pars[21:], logits)
+            gpu.decode_step(toks[23].clone(), logits)
+            more = [c2.cpu().numpy(), logits.cpu().numpy()]
+        out.append((step, list(active), toks.cpu().numpy(), pars.cpu().numpy(), cum.cpu().numpy(), *more))
+        gpu.close()
+    a, b = out
+    assert a[0] == b[0] and a[1] == b[1] and len(a) == len(b)
+    assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
+    for x, y in zip(a[4:], b[4:]):
+        fin = np.isfinite(y)
+        assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
