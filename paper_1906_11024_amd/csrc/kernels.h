@@ -54,6 +54,20 @@ hipError_t launch_gemm_split(const GemmParams& p, int wm, hipStream_t stream);
 // *flag = 1 if one of the n fp32 parameters is 2^16 or larger, or not finite (gemm_split.hip cannot take the model)
 hipError_t launch_check_splittable(const float* w, size_t n, int* flag, hipStream_t stream);
 
+// bf16 only: the same product with its operands straight to LDS (gemm_lds.hip); variant: gemm_lds_variant.  launch_gemm
+// takes it by itself where that says so.  It loads and stores 16 bytes at a time: gemm_lds_aligned (the logits go where the
+// caller wants them, every other operand is the library's own and aligned).
+inline bool gemm_lds_aligned(const GemmParams& p) {
+  auto at16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
+  if (!at16(p.A) || !at16(p.W) || p.lda % 8 || (p.bias && reinterpret_cast<uintptr_t>(p.bias) % 8)) return false;
+  if (p.out_kind == 3) return true;
+  const int per = p.out_kind == 0 ? 8 : 4;
+  for (int i = 0; i < 3; ++i)
+    if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % per || p.tstride[i] % per)) return false;
+  return p.N % per == 0 && (p.seg_w >= p.N || (p.out_kind == 0 && p.seg_w % per == 0));
+}
+hipError_t launch_gemm_lds(const GemmParams& p, int variant, hipStream_t stream);
+
 // A second update + LayerNorm applied to a first one's output in the same launch:
 // out = LN2(LN1(...) + sum_s part2[s][m] + bias2)
 struct LnStage2 {
@@ -244,6 +258,7 @@ struct SmallLayer {            // device array, one per decoder layer
   float *Kc, *Vc;              // [position][cache_rows][d]
   float *S_self, *S_ctx;       // weights a head writes for its followers (null: none), a follower reads
   const float *mem_k, *mem_v;
+  float *dbg_A_self, *dbg_A_ctx, *dbg_hidden;   // null, or copies for inspection [rows][d]; S_ctx of a head is then zero past the sentence
 };
 struct SmallDecode {
   const SmallLayer* layers; int n_layers;

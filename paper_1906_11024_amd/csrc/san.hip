@@ -603,7 +603,7 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
       HIP_TRY(c, hipMemset(c->t_dev, 0, 256));
     }
     c->weights.clear();
-    if (c->dt == SAN_F32 && !aan && !nocache && !cfg->debug && small_model_faster(c->d, c->F, c->V, Ld, cfg->beam, 1)) {
+    if (c->dt == SAN_F32 && !aan && !nocache && !(cfg->debug & 2) && small_model_faster(c->d, c->F, c->V, Ld, cfg->beam, 1)) {
       std::vector<SmallLayer> sl(Ld);
       for (int n = 0; n < Ld; ++n) {
         const DecLayer &L = c->dec[n], &Hd = c->dec[L.ctx_head];
@@ -619,8 +619,10 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
         o.Kc = (float*)L.Kc; o.Vc = (float*)L.Vc;
         const bool self_shared = !o.self_head || (n + 1 < Ld && c->dec[n + 1].self_head == n);
         const bool ctx_shared = shareS && (!o.ctx_head || (n + 1 < Ld && c->dec[n + 1].ctx_head == n));
-        o.S_self = self_shared ? c->dec[L.self_head].S_self : nullptr;
-        o.S_ctx = ctx_shared ? Hd.S_ctx : nullptr;
+        const bool dbg = (cfg->debug & 1) != 0;
+        o.dbg_A_self = L.dbg_A_self; o.dbg_A_ctx = L.dbg_A_ctx; o.dbg_hidden = L.dbg_hidden;
+        o.S_self = self_shared || dbg ? c->dec[L.self_head].S_self : nullptr;
+        o.S_ctx = ctx_shared || (dbg && o.ctx_head) ? Hd.S_ctx : nullptr;
         o.mem_k = f(L.mem);
         o.mem_v = o.ctx_head ? f(L.mem) + d : f(L.mem);
       }

@@ -406,6 +406,8 @@ __global__ __launch_bounds__(kSmThreads) void small_decode_kernel(SmallDecode P)
           float* const S = L.S_ctx ? L.S_ctx + ((size_t)(row0 + r) * H + hd) * P.max_src_cap : nullptr;
           attend<lanes.value>(q + r * d + hd * dh, L.mem_k + hd * dh, L.mem_v + hd * dh,
                  [&](int j) { return (mem0 + j) * L.ctx_ld; }, n_src, dh, P.scale, !L.ctx_head, S, p, actx + r * d + hd * dh);
+          if (L.dbg_hidden && L.ctx_head)   // copies for inspection: zeros past the sentence
+            for (int j = n_src + (tid & (lanes.value - 1)); j < P.max_src; j += lanes.value) S[j] = 0.f;
         });
       narrow(actx, L.wo_c, L.bo_c, to_y);
       const SmNorm n3 = request_norm(L.ln3g, L.ln3b, d);
@@ -414,6 +416,14 @@ __global__ __launch_bounds__(kSmThreads) void small_decode_kernel(SmallDecode P)
       wide(x, L.w1, L.b1, F, [&](int r, int c, float v) { h[r * F + c] = fmaxf(v, 0.f); });
       product_f<RB>(h, F, L.w2, L.b2, d, R, to_y);
       norm_rows(y, x, n3, d, R, P.eps);
+      if (L.dbg_hidden) {   // copies for inspection
+        __syncthreads();
+        for (int i = tid; i < R * d; i += kSmThreads) {
+          L.dbg_A_self[(size_t)row0 * d + i] = a[i];
+          L.dbg_A_ctx[(size_t)row0 * d + i] = actx[i];
+          L.dbg_hidden[(size_t)row0 * d + i] = x[i];
+        }
+      }
     }
     if (!search) {
       float* const out = P.logits + (size_t)row0 * V;
