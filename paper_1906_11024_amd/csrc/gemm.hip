@@ -394,6 +394,8 @@ static hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
 // (fp32: the split kernel's tile wherever that one is the faster, also for models that have to do without it)
 static int cand_pick_tile(int M, int N, int K, int dtype) {
   if (dtype == 0 && gemm_split_shape(M, N, K, 1, 1).wm) return 1;
+  if (dtype == 1)
+    if (const int v = gemm_lds_variant(M, N, K, 3, 1, false)) return kLdsModels[v - 1].bn == 256 ? 2 : 1;
   return gemm_pick_tile(M, N, K, dtype, false);
 }
 int gemm_cand_tile_n(int M, int N, int K, int dtype) {
@@ -412,9 +414,8 @@ static hipError_t launch_gemm_cand(int dtype, const GemmParams& p, bool plain, h
     return hipErrorInvalidValue;
   const int tile = cand_pick_tile(p.M, p.N, p.K, dtype);
   if (dtype == 1) {
-    if (tile == 2) return launch_tile<bf16_t, 4, 4, 2, 2, 1, 2, 128, true>(p, stream);
+    if (const int v = gemm_lds_variant(p.M, p.N, p.K, 3, 1, false)) return launch_gemm_lds(p, v, stream);
     if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256, true>(p, stream);
-    if (tile == 1) return launch_tile<bf16_t, 4, 2, 1, 2, 1, 2, 128, true>(p, stream);
     if (p.K % 128 == 0) return launch_tile<bf16_t, 2, 2, 1, 1, 1, 2, 256, true>(p, stream);
     return launch_tile<bf16_t, 2, 2, 1, 1, 1, 4, 128, true>(p, stream);
   }
@@ -440,6 +441,8 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
     const SplitShape sp = gemm_split_shape(p.M, p.N, p.K, p.ksplit, p.ksplit);
     if (sp.wm) return launch_gemm_split(p, sp.wm, stream);
   }
+  if (dtype == 1 && gemm_lds_aligned(p))
+    if (const int v = gemm_lds_variant(p.M, p.N, p.K, p.out_kind, p.ksplit, (p.flags & kGemmRagged) != 0)) return launch_gemm_lds(p, v, stream);
   int tile = gemm_pick_tile(p.M, p.N, p.K, dtype, p.out_kind == 2);
   if (p.ksplit > 1 && tile != 3) tile = 0;   // only the small tiles split k across blocks
   // A wave's MFMA chain over the whole k range is what bounds a small GEMM, and
@@ -456,14 +459,12 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
     else if (tiles64 <= 192 && chunks >= 4) shape = 1;
   }
   if (dtype == 1) {
-    if (tile == 2) return launch_tile<bf16_t, 4, 4, 2, 2, 1, 2>(p, stream);
     if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256>(p, stream);
-    if (wide && tile != 1) {   // (the 128x128 tile with wide chunks would not fit two blocks per CU: slower)
+    if (wide) {
       if (shape == 2) return launch_tile<bf16_t, 1, 1, 1, 1, 4, 2, 256>(p, stream);
       if (shape == 1) return launch_tile<bf16_t, 2, 1, 1, 1, 2, 2, 256>(p, stream);
       return launch_tile<bf16_t, 2, 2, 1, 1, 1, 2, 256>(p, stream);
     }
-    if (tile == 1) return launch_tile<bf16_t, 4, 2, 1, 2, 1, 2>(p, stream);
     if (shape == 2) return launch_tile<bf16_t, 1, 1, 1, 1, 4, 4>(p, stream);
     if (shape == 1) return launch_tile<bf16_t, 2, 1, 1, 1, 2, 4>(p, stream);
     return chunks <= 3 ? launch_tile<bf16_t, 2, 2, 1, 1, 1, 2>(p, stream) : launch_tile<bf16_t, 2, 2, 1, 1, 1, 4>(p, stream);

@@ -99,22 +99,65 @@ inline bool small_model_faster(int d, int F, int V, int layers, int beam, int ba
   return (float)((batch + 255) / 256) * (6.f + 6.2f * layers + (5.f + 4.f * beam) * mb) <= 0.85f * (21.f + 27.f * layers);
 }
 
-// Tile choice: 0 = 64x64 or smaller (2x2 waves and the k-group shapes below);
-// 1 = 128x128 once that still gives ~one block per CU (the output layer);
-// 2 = 256x256 (bf16 only) once that does; 3 = see below.  The wide output layer is bound by
-// the operand traffic between L2 and the CUs, |X| * N/BN + |W| * M/BM, so the
-// biggest tile that still fills the chip wins: measured on the output layer,
-// fp32 M = 256: 128x128 with 16 waves 69 us (8 waves 81, 256x128 71-76, 256x256
-// 132: half the CUs idle); bf16 M = 512: 256x256 with 16 waves 44-48 us (128x128
-// 63, 256x128 51, 128x256 55).
-// 3 = 64x128 with 8 waves and 256-byte chunks (bf16 only, K % 128 == 0): the bf16
-// decode GEMMs are bound by the same operand traffic (their MFMA time is
-// negligible), and this tile moves 25-30 % fewer bytes than 64x64 at the same
-// block count after splitting k (Big FFN-1 11.9 -> 9.6 us, FFN-2 12.4 -> 10.7).
+// bf16 products with their operands straight to LDS (gemm_lds.hip): which tile, or 0 for gemm_kernel.  kind: GemmParams::
+// out_kind; ragged: M is the padded row count of a batch whose words lie back to back.
+//   1 64 x 64, chunks of 128   2 64 x 64, four chunks of 64   3 128 x 128   4 192 x 128   5 256 x 256   6 320 x 256
+//   7 128 x 64, four chunks of 64
+// A model of each, in us: 2 + the larger of one block alone on its CU, e1 + g1 k / 512, and of n blocks on a CU one
+// after the other or two at a time, n (e2 + g2 k / 512), n between the tiles per CU and that rounded up (q: how near the
+// former).  Fitted to 142 shapes of 64 to 15300 rows; over them the choice costs 0.4 % against the best of them, 10 % at
+// worst.  Products with candidates (the last three lines) pay their selection too.  1, and 2 with more tiles than CUs, hold
+// a chunk or two in flight per block: enough for k of 512, but the weights of wider models come from HBM (512 x 4096 x 1024 with
+// weights of 320 MB: 1 11.5, 2 11.8, 7 10.1, gemm_kernel 11.5).
+// gemm_kernel keeps: products split over blocks whose parts of k are short (1024 x 512 x 2048 in four 6.9 / 7.25,
+// 512 x 1024 x 1024 in four 5.5 / 5.6; but 512 x 1024 x 4096 in four 11.8 / 11.5, 301 rows 10.3 / 9.5); few tiles with a long
+// k, which it splits over the waves of a block (1024 x 512 x 2048 9.8 / 10.9, 512 x 1024 x 1024 6.5 / 6.7, 68 x 4096 x 1024
+// 6.7 / 7.3); output layers of candidates with few tiles (40 x 32000 x 512 10.0 / 11.8, 256 x 8000 9.2 / 11.3; 68 x 32000
+// 15.2 / 11.7, 300 28.7 / 21.2, 700 48.7 / 38.3).  Padding is a quarter to a half of a ragged batch: 0.7 of it stand for M.
+struct LdsModel { int bm, bn; float e1, g1, e2, g2, q; };
+constexpr int kLdsVariants = 7;
+constexpr LdsModel kLdsModels[kLdsVariants] = {
+    {64, 64, 0.65f, 2.28f, 0.88f, 1.73f, 0.55f},   {64, 64, 1.09f, 2.01f, 0.91f, 1.72f, 0.46f},
+    {128, 128, 0.41f, 4.71f, 1.22f, 4.43f, 0.35f}, {192, 128, 3.81f, 0.54f, 2.12f, 5.49f, 0.22f},
+    {256, 256, 0.67f, 11.19f, 4.70f, 10.95f, 0.f}, {320, 256, 2.81f, 8.57f, 6.85f, 12.66f, 0.f},
+    {128, 64, 1.90f, 2.30f, 2.00f, 2.30f, 0.1f}};
+constexpr LdsModel kLdsCandModels[3] = {   // of 3, 4 and 5
+    {128, 128, 0.8f, 9.6f, 1.0f, 5.0f, 0.3f}, {192, 128, 2.5f, 10.f, 2.7f, 5.8f, 0.2f}, {256, 256, 12.7f, 13.4f, 12.7f, 13.4f, 0.f}};
+inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragged) {
+  if (M <= 16 || N < 64 || ksplit < 1 || K % (64 * ksplit)) return 0;
+  const int k = K / ksplit;
+  const bool cand = kind == 3;
+  if (ragged) M = M - M * 3 / 10;
+  if (cand && (M <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
+  if (ksplit > 1 && k < 1024) return 0;
+  const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
+  if (!cand && k >= 1024 && tiles64 <= 128) return 0;
+  int best = 0;
+  float best_us = 0.f;
+  for (int v = 1; v <= kLdsVariants; ++v) {
+    if (cand ? v < 3 || v > 5 : (v == 1 && (k % 128 || k > 512)) || (v == 2 && k > 512 && tiles64 > 256)) continue;
+    const LdsModel& m = cand ? kLdsCandModels[v - 3] : kLdsModels[v - 1];
+    const float tiles = (float)((M + m.bm - 1) / m.bm) * (float)((N + m.bn - 1) / m.bn) * (float)ksplit / 256.f;
+    const float n = (1.f - m.q) * (float)(long)(tiles + 0.9999f) + m.q * (tiles > 1.f ? tiles : 1.f);
+    const float one = m.e1 + m.g1 * (float)k / 512.f, all = n * (m.e2 + m.g2 * (float)k / 512.f);
+    // candidates of 128 columns: the search reads twice the slots
+    const float us = 2.f + (one > all ? one : all) + (cand && m.bn == 128 ? 2.f + 0.004f * (float)M : 0.f);
+    if (!best || us < best_us) { best = v; best_us = us; }
+  }
+  return best;
+}
+
+// Tile choice of gemm_kernel: 0 = 64x64 or smaller (2x2 waves and the k-group shapes of launch_gemm);
+// 1 = 128x128 (fp32 only) once that still gives ~one block per CU (the output layer of models that gemm_split.hip cannot
+// take): the wide output layer is bound by the operand traffic between L2 and the CUs, |X| * N/BN + |W| * M/BM, so the
+// biggest tile that still fills the chip wins: M = 256 128x128 with 16 waves 69 us (8 waves 81, 256x128 71-76, 256x256
+// 132: half the CUs idle).
+// 3 = 64x128 with 8 waves and 256-byte chunks (bf16 only, K % 128 == 0): the products split over blocks
+// are bound by the same operand traffic (their MFMA time is negligible), and this tile moves 25-30 % fewer bytes than
+// 64x64 at the same block count after splitting k (512 x 1024 x 4096 12.4 -> 10.7 us).
 // can_split: the GEMM writes partials, so k may be divided over up to 4 blocks to fill the chip
 inline int gemm_pick_tile(int M, int N, int K, int dtype, bool can_split) {
-  if (dtype == 1 && M >= 256 && (long)((M + 255) / 256) * ((N + 255) / 256) >= 200) return 2;
-  if (M >= 128 && (long)((M + 127) / 128) * ((N + 127) / 128) >= 200) return 1;
+  if (dtype == 0 && M >= 128 && (long)((M + 127) / 128) * ((N + 127) / 128) >= 200) return 1;
   if (dtype == 1 && K % 128 == 0 && (long)((M + 63) / 64) * ((N + 127) / 128) >= (can_split ? 64 : 160)) return 3;
   return 0;
 }
@@ -127,7 +170,7 @@ inline int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain) {
     if (sp.wm) return sp.ks;
   }
   const int tile = gemm_pick_tile(M, N, K, dtype, true);
-  if (tile == 1 || tile == 2) return 1;
+  if (tile == 1) return 1;
   int ks = 1;
   if (tile == 3) {
     const int nchunks = K / 128;   // 256-byte chunks

@@ -443,3 +443,58 @@ def test_small_models_loop_equals_the_launches(eos, compact, beam):
     for x, y in zip(a[4:], b[4:]):
         fin = np.isfinite(y)
         assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
+
+
+# bf16 products with their operands straight to LDS, every tile of them: (row counts, widths) whose products take it, rows and
+# columns that do not fill the last tile, q/k/v segments, fp32 partials split or not, ragged encoders, candidates, vocabularies
+# that end inside a tile.  Checked: a few sentences (a product's rows do not depend on each other), the last ones among them.
+_LDS = {   # case: (variant, (M, N, K, kind, k split, ragged) of the product meant, configuration)
+    "64x64": (1, (41, 2048, 512, 0, 1, 0), dict(batch=41, d=512, H=8, F=2048)),
+    "64x64_four_stages": (2, (301, 3072, 1024, 0, 1, 0), dict(batch=301, d=1024, H=16, F=1088, src_len=(1, 2))),
+    "128x64_split": (7, (301, 1024, 4096, 2, 4, 0), dict(batch=301, d=1024, H=16, F=4096, src_len=(1, 2))),
+    "128x128_ragged": (3, (2440, 2048, 512, 0, 1, 1), dict(batch=40, d=512, H=8, F=2048, src_len=(1, 61))),
+    "192x128_ragged": (4, (15250, 512, 512, 2, 1, 1), dict(batch=250, d=512, H=8, F=192, src_len=(1, 61), steps=1)),
+    "256x256": (5, (9150, 2048, 512, 0, 1, 1), dict(batch=150, d=512, H=8, F=2048, src_len=(1, 61), steps=1)),
+    "320x256": (6, (7930, 3072, 1024, 0, 1, 1), dict(batch=130, d=1024, H=16, F=128, src_len=(1, 61), steps=1)),
+    "128x128_candidates": (3, (68, 32004, 512, 3, 1, 0), dict(batch=17, beam=4, d=512, H=8, V=32004)),
+    "192x128_candidates": (4, (300, 32004, 512, 3, 1, 0), dict(batch=75, beam=4, d=512, H=8, V=32004, src_len=(1, 2))),
+    "256x256_candidates": (5, (500, 32004, 512, 3, 1, 0), dict(batch=125, beam=4, d=512, H=8, V=32004, src_len=(1, 2))),
+}
+
+
+@pytest.mark.parametrize("case", sorted(_LDS))
+def test_bf16_products_straight_to_lds_match_oracle(case):
+    variant, product, kw = _LDS[case]
+    assert rules.lib().lds_variant(*product) == variant
+    cfg = _cfg(dtype="bf16", n_enc=1, n_dec=2, self_pi=[1, 1], encdec_pi=[2], steps=2, **{k: v for k, v in kw.items() if k != "steps"})
+    cfg["steps"] = kw.get("steps", 2)
+    w = wl.make_weights(cfg, seed=31, sharp=4.0)
+    w["w_out"] = wl.round_to_bf16(w["w_out"] * np.float32(8.0))
+    src, lens = wl.make_source(cfg, 31)
+    n = cfg["batch"]
+    gpu = hz.make_gpu(cfg, w)
+    ls = hz.Lockstep(gpu, hz.make_oracle(cfg, w), src, lens, cfg["beam"], subset=np.unique([0, n // 3, n - 2, n - 1]),
+                     loop="cands" if product[3] == 3 else None)
+    for _ in range(cfg["steps"]):
+        ls.step(logit_tol=BF16_TOL)
+    if product[3] != 3:
+        assert max(ls.log["logit_err"]) <= BF16_TOL, max(ls.log["logit_err"])
+    gpu.close()
+
+
+# The logits may lie on any 4-byte boundary: no 16-byte stores there.  The same sums in either kernel, up to their order.
+@pytest.mark.parametrize("rows", [40, 300])
+def test_bf16_logits_on_a_4_byte_boundary(rows):
+    cfg = _cfg(dtype="bf16", batch=rows, d=512, H=8, F=192, V=16004, src_len=(1, 2))
+    w = wl.make_weights(cfg, seed=3)
+    src, lens = wl.make_source(cfg, 3)
+    gpu = hz.make_gpu(cfg, w)
+    buf = torch.zeros(2, rows * cfg["V"] + 8, device="cuda")
+    tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+    for i, off in enumerate((0, 1)):
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        gpu.decode_step(tok, buf[i, off:off + rows * cfg["V"]].view(rows, cfg["V"]))
+    a, b = buf[0, :rows * cfg["V"]].cpu().numpy(), buf[1, 1:1 + rows * cfg["V"]].cpu().numpy()
+    assert buf[1, 0] == 0 and (buf[1, 1 + rows * cfg["V"]:] == 0).all()
+    assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max()
+    gpu.close()

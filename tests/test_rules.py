@@ -22,3 +22,19 @@ def test_rules_stay_within_the_kernels_limits():
         assert not L.few_rows(dt, rows, d) or (rows <= 16 and d <= 1024)
     for n in (4, 1000, 18428, 18432, 32000):
         assert L.cand_n(n) in (64, 128)
+
+
+def test_bf16_products_get_a_tile_that_can_take_them():
+    L = rules.lib()
+    chunk = [128, 64, 64, 64, 64, 64, 64]
+    seen = set()
+    for kind, ragged in ((0, 0), (0, 1), (1, 0), (2, 0), (2, 1), (3, 0)):
+        for m, n, k in itertools.product((1, 16, 17, 63, 64, 65, 128, 129, 300, 512, 1000, 2048, 9000, 15300), (4, 64, 512, 1004, 3072, 4096, 32000),
+                                         (64, 128, 192, 512, 576, 1024, 4096)):
+            for ks in (1, 2, 4, 8) if kind == 2 else (1,):
+                v = L.lds_variant(m, n, k, kind, ks, ragged)
+                assert 0 <= v <= 7
+                if v:
+                    seen.add((kind, v))
+                    assert m > 16 and n >= 64 and k % (chunk[v - 1] * ks) == 0 and (kind != 3 or 3 <= v <= 5)
+    assert {v for _, v in seen} == set(range(1, 8)) and {v for kd, v in seen if kd == 3} == {3, 4, 5}
