@@ -130,6 +130,7 @@ inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragg
   if (ragged) M = M - M * 3 / 10;
   if (cand && (M <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
   if (ksplit > 1 && k < 1024) return 0;
+  if (!cand && M <= 256 && k <= 512) return 0;   // 5 to 15 us of a 460 us pass over 16 sentences of up to 9 words
   const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   if (!cand && k >= 1024 && tiles64 <= 128) return 0;
   int best = 0;
