@@ -440,24 +440,16 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
   if (dtype == 0 && !plain) {
     const SplitShape sp = gemm_split_shape(p.M, p.N, p.K, p.ksplit, p.ksplit);
     if (sp.wm) return launch_gemm_split(p, sp.wm, stream);
+    // padding or not, the padded rows choose: a ragged batch gets the bits of a padded one
+    if (gemm_kwaves_aligned(p) && gemm_pick_tile(p.M, p.N, p.K, 0, p.out_kind == 2) == 0)
+      if (const int v = gemm_kwaves_variant(p.M, p.N, p.K, p.ksplit)) return launch_gemm_kwaves(p, v, stream);
   }
   if (dtype == 1 && gemm_lds_aligned(p))
     if (const int v = gemm_lds_variant(p.M, p.N, p.K, p.out_kind, p.ksplit, (p.flags & kGemmRagged) != 0)) return launch_gemm_lds(p, v, stream);
   int tile = gemm_pick_tile(p.M, p.N, p.K, dtype, p.out_kind == 2);
   if (p.ksplit > 1 && tile != 3) tile = 0;   // only the small tiles split k across blocks
-  // A wave's MFMA chain over the whole k range is what bounds a small GEMM, and
-  // only waves on different SIMDs run their chains in parallel.  When 64x64 tiles
-  // would leave most SIMDs idle, use smaller tiles and deal each tile's k range to
-  // 2 or 4 wave groups (reduced through LDS), aiming at ~one wave per SIMD:
-  //   shape 1: 64x32 tiles, 2 waves x 2 k-groups;  shape 2: 32x32 tiles, 1 wave x 4 k-groups.
-  // (64x32 with 4 k-groups, 32x64 and 64x64 with 2, 32x32 with 8 all measured within 3% of these.)
   const int chunks = (p.K / (dtype == 1 ? 64 : 32) + p.ksplit - 1) / p.ksplit;   // in 128-byte units
-  const long tiles64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64) * p.ksplit;
-  int shape = 0;
-  if (tile == 0) {
-    if (tiles64 <= 64 && chunks >= 8) shape = 2;
-    else if (tiles64 <= 192 && chunks >= 4) shape = 1;
-  }
+  const int shape = tile == 0 ? gemm_tile_shape(p.M, p.N, p.ksplit, chunks) : 0;
   if (dtype == 1) {
     if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256>(p, stream);
     if (wide) {

@@ -29,13 +29,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// 16 bytes per lane from base + off (bytes) straight to LDS at lds + 16 * lane (lds: byte offset, uniform).  Counted by
-// vmcnt like any load; the compiler does not know of it, so the waits stand in the kernel.
-__device__ __forceinline__ void load_to_lds(const void* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
-
 // WM x WN waves, each TM x TN tiles of 32 x 32; k in chunks of BK, ST chunks of LDS.
 template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND>
 __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {

@@ -68,6 +68,17 @@ inline bool gemm_lds_aligned(const GemmParams& p) {
 }
 hipError_t launch_gemm_lds(const GemmParams& p, int variant, hipStream_t stream);
 
+// fp32 only: small products through bf16 parts with k dealt to the waves of a block (gemm_kwaves.hip); variant:
+// gemm_kwaves_variant.  launch_gemm takes it by itself where that says so, unless `plain` is set.  16 bytes at a time.
+inline bool gemm_kwaves_aligned(const GemmParams& p) {
+  auto at16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
+  if (!at16(p.A) || !at16(p.W) || p.lda % 4 || (p.bias && !at16(p.bias))) return false;
+  for (int i = 0; i < 3; ++i)
+    if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % 4 || p.tstride[i] % 4)) return false;
+  return p.N % 4 == 0 && (p.seg_w >= p.N || p.seg_w % 4 == 0);
+}
+hipError_t launch_gemm_kwaves(const GemmParams& p, int variant, hipStream_t stream);
+
 // A second update + LayerNorm applied to a first one's output in the same launch:
 // out = LN2(LN1(...) + sum_s part2[s][m] + bias2)
 struct LnStage2 {

@@ -163,6 +163,56 @@ inline int gemm_pick_tile(int M, int N, int K, int dtype, bool can_split) {
   return 0;
 }
 
+// The smaller tiles of gemm_kernel: a wave's MFMA chain over the whole k range is what bounds a small product, and only waves
+// on different SIMDs run their chains in parallel.  When 64x64 tiles would leave most SIMDs idle, smaller tiles deal their
+// k range to 2 or 4 wave groups (reduced through LDS), aiming at ~one wave per SIMD:
+//   0: 64x64   1: 64x32 tiles, 2 waves x 2 k-groups   2: 32x32 tiles, 1 wave x 4 k-groups
+// (64x32 with 4 k-groups, 32x64 and 64x64 with 2, 32x32 with 8 all measured within 3% of these.)  chunks: k in 128-byte units
+inline int gemm_tile_shape(int M, int N, int ksplit, int chunks) {
+  const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
+  return tiles64 <= 64 && chunks >= 8 ? 2 : tiles64 <= 192 && chunks >= 4 ? 1 : 0;
+}
+
+// Small fp32 products through bf16 parts with k dealt to the waves (gemm_kwaves.hip): which tile, or 0 for gemm_kernel.
+//   1 32 x 32, 8 waves   2 64 x 32, 8 waves   3 64 x 64, 4 waves   4 32 x 32, 4 waves
+// A model of each and of gemm_kernel's three shapes, in us: the larger of one block alone on its CU, e1 + g1 k / 512, and of n
+// blocks on a CU, n (e2 + g2 k / 512), n between the tiles per CU and that rounded up (q: how near the former), and 2 for the
+// launch.  Fitted to 283 shapes of 17 to 700 rows, k 256 to 4096, up to 1.6e9 multiplications (beyond, it is not asked), with
+// an error of 5 to 12 %; over them the choice takes 0.89 of gemm_kernel's time, 1 % more than the best of all would.
+// Measured (us, gemm_kernel / here; kernel alone): 64 x 512 x 512 6.8 / 5.2, 128 x 2048 x 512 7.1 / 5.9, 256 rows 9.2 / 8.7,
+// 300 rows 13.4 / 10.0, 128 x 1536 x 512 7.0 / 5.7, 256 rows 8.9 / 7.9, 256 x 768 x 256 5.0 / 4.4, 256 x 3072 x 1024 24.3 / 18.3,
+// 64 x 512 x 512 in eight 4.1 / 3.5, 300 x 512 x 2048 in eight 12.2 / 10.2.  Left to gemm_kernel: 256 x 512 x 512 in eight
+// 4.4 / 4.7, 256 x 512 x 2048 in eight 8.3 / 9.2; more than 32 rows by columns whose weights do not stay near (256 x 8000 x 512
+// 22.9 / 25.1, 64 rows 9.3 / 9.6, but 20 rows 9.1 / 6.2); 64 x 64 tiles with k split (128 x 1024 x 4096 in eight 13.5 / 14.4).
+struct KwavesModel { int bm, bn, kw; float e1, g1, e2, g2, q; };
+constexpr KwavesModel kKwavesModels[4] = {
+    {32, 32, 8, 1.09f, 2.26f, 0.82f, 2.40f, 0.15f}, {64, 32, 8, -1.97f, 3.83f, 2.02f, 3.42f, 0.f},
+    {64, 64, 4, -2.48f, 5.48f, 3.49f, 5.05f, 0.f},  {32, 32, 4, 1.14f, 2.67f, 0.52f, 2.57f, 0.18f}};
+constexpr KwavesModel kTileModels[3] = {   // gemm_kernel, by gemm_tile_shape
+    {64, 64, 0, 0.91f, 10.27f, 0.93f, 9.61f, 0.23f}, {64, 32, 0, 1.54f, 5.40f, 1.22f, 5.01f, 0.19f},
+    {32, 32, 0, 1.17f, 3.68f, 1.29f, 3.25f, 0.09f}};
+constexpr float kKwavesMost = 1.6e9f;
+inline int gemm_kwaves_variant(int M, int N, int K, int ksplit) {
+  if (M < 1 || N < 4 || N % 4 || K < 64 || ksplit < 1 || (float)M * (float)N * (float)K > kKwavesMost) return 0;
+  if (M > 32 && N > 8 * K) return 0;
+  auto us_of = [&](const KwavesModel& m) {
+    const float k = (float)K / (float)ksplit / 512.f;
+    const float tiles = (float)((M + m.bm - 1) / m.bm) * (float)((N + m.bn - 1) / m.bn) * (float)ksplit / 256.f;
+    const float n = (1.f - m.q) * (float)(long)(tiles + 0.9999f) + m.q * (tiles > 1.f ? tiles : 1.f);
+    const float one = m.e1 + m.g1 * k, all = n * (m.e2 + m.g2 * k);
+    return 2.f + (one > all ? one : all);
+  };
+  int best = 0;
+  float best_us = 0.95f * us_of(kTileModels[gemm_tile_shape(M, N, ksplit, (K / 32 + ksplit - 1) / ksplit)]);
+  for (int v = 1; v <= 4; ++v) {
+    const KwavesModel& m = kKwavesModels[v - 1];
+    if (K % (16 * m.kw * ksplit) || (v == 3 && ksplit > 1)) continue;
+    const float us = us_of(m);
+    if (us < best_us) { best_us = us; best = v; }
+  }
+  return best;
+}
+
 // split factor that fills the chip for an M x N x K product (1 when the tiles alone already do)
 // plain: fp32 without splitting into bf16 parts
 inline int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain) {

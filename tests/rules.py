@@ -14,6 +14,7 @@ extern "C" int few_rows(int dtype, int rows, int d) { return san::few_rows_faste
 extern "C" int skinny(int dtype, int M, int N, int K, int kind, int ks) { return san::gemm_skinny_faster(dtype, M, N, K, kind, ks); }
 extern "C" int small_model(int d, int F, int V, int layers, int beam, int batch) { return san::small_model_faster(d, F, V, layers, beam, batch); }
 extern "C" int lds_variant(int M, int N, int K, int kind, int ks, int ragged) { return san::gemm_lds_variant(M, N, K, kind, ks, ragged != 0); }
+extern "C" int kwaves_variant(int M, int N, int K, int ks) { return san::gemm_kwaves_variant(M, N, K, ks); }
 extern "C" int cand_n(int N) { return san::gemm_skinny_cand_n(N); }
 extern "C" int pick_ksplit(int M, int N, int K, int dtype) { return san::gemm_pick_ksplit(M, N, K, dtype, false); }
 """

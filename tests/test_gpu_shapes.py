@@ -498,3 +498,77 @@ def test_bf16_logits_on_a_4_byte_boundary(rows):
     assert buf[1, 0] == 0 and (buf[1, 1 + rows * cfg["V"]:] == 0).all()
     assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max()
     gpu.close()
+
+
+# fp32 products with k dealt to the waves, every tile of them: rows and columns that do not fill the last tile, q/k/v
+# segments, fp32 partials, one piece of 16 k-values per wave and many, ragged encoders (rows of 128 columns above).
+_KWAVES = {   # case: (variant, (M, N, K, k split) of the product meant, configuration)
+    "32x32_eight_waves": (1, (41, 2048, 512, 1), dict(batch=41, d=512, H=8, F=2048)),
+    "32x32_one_piece": (1, (33, 576, 128, 1), dict(batch=33, d=192, H=3, F=128, V=576)),
+    "64x32": (2, (185, 1536, 512, 1), dict(batch=185, d=512, H=8, F=512, src_len=(1, 2))),
+    "64x64": (3, (185, 3072, 1024, 1), dict(batch=185, d=1024, H=16, F=64, src_len=(1, 2))),
+    "32x32_four_waves": (4, (45, 192, 64, 1), dict(batch=45, d=64, H=4, F=192, beam=1, V=2004, n_dec=5, self_pi=[5], encdec_pi=[5])),
+    "32x32_split": (4, (65, 512, 512, 8), dict(batch=13, beam=5, d=512, H=8, F=64)),
+}
+
+
+@pytest.mark.parametrize("case", sorted(_KWAVES))
+def test_fp32_products_dealt_to_waves_match_oracle(case):
+    variant, product, kw = _KWAVES[case]
+    assert rules.lib().kwaves_variant(*product) == variant and rules.lib().split_wm(*product[:3], product[3], product[3]) == 0
+    if product[3] > 1:
+        assert rules.lib().pick_ksplit(*product[:3], 0) == product[3]
+    ls = _lockstep(_cfg(steps=2, **kw))
+    assert max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
+    ls.gpu.close()
+
+
+# Logits on any 4-byte boundary: no 16-byte stores there, and the fp32 instructions round otherwise (2^-24 of the products'
+# absolute sum at most once per k-value; here 512 of them, of random signs).
+def test_fp32_logits_on_a_4_byte_boundary():
+    rows = 40
+    cfg = _cfg(batch=rows, d=512, H=8, F=64)
+    assert rules.lib().kwaves_variant(rows, cfg["V"], 512, 1) > 0
+    w = wl.make_weights(cfg, seed=3)
+    src, lens = wl.make_source(cfg, 3)
+    gpu = hz.make_gpu(cfg, w)
+    buf = torch.zeros(2, rows * cfg["V"] + 8, device="cuda")
+    tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+    for i in (0, 1):
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        gpu.decode_step(tok, buf[i, i:i + rows * cfg["V"]].view(rows, cfg["V"]))
+    a, b = buf[0, :rows * cfg["V"]].cpu().numpy(), buf[1, 1:1 + rows * cfg["V"]].cpu().numpy()
+    assert buf[1, 0] == 0 and (buf[1, 1 + rows * cfg["V"]:] == 0).all()
+    assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max()
+    gpu.close()
+
+
+@pytest.mark.parametrize("operands", ["normal", "spread", "relu", "one_live", "below_half_step", "signed_half_step"])
+def test_products_dealt_to_waves_are_no_further_from_64_bits(operands):
+    """As test_split_products_are_no_further_from_64_bits."""
+    V, d, batch = 1004, 512, 40
+    assert rules.lib().kwaves_variant(batch, V, d, 1) == 1
+    rng = np.random.default_rng(11)
+    row, w_out = rng.normal(size=d), 0.02 * rng.normal(size=(V, d))
+    step = np.nextafter(np.float32(1.00390625), np.float32(0))
+    if operands == "spread":
+        row, w_out = row * np.exp(rng.uniform(-8, 8, d)), w_out * np.exp(rng.uniform(-8, 8, (V, d)))
+    elif operands == "relu":
+        row = np.maximum(row, 0)
+    elif operands == "one_live":
+        row[np.arange(d) != 77] = 0
+    elif operands == "below_half_step":
+        row, w_out = np.full(d, step), np.full((V, d), step)
+    elif operands == "signed_half_step":
+        row, w_out = step * np.sign(row), step * np.sign(w_out)
+    row, w_out = row.astype(np.float32), w_out.astype(np.float32)
+    cfg = _cfg(batch=batch, d=d, H=8, F=64, V=V, n_dec=1, self_pi=[1], encdec_pi=[1])
+    exact = w_out.astype(np.float64) @ row.astype(np.float64)
+    err = []
+    for debug in (0, 2):
+        got = _logits_of(cfg, row, w_out, debug)
+        assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+        err.append(np.linalg.norm(got[0] - exact) / np.linalg.norm(exact))
+    # 1 % for the roundings of the last additions; a sum per wave, joined in seven
+    assert err[0] <= 1.01 * err[1], err
+    assert err[0] <= 4 * np.sqrt(d / 16 + 8) * 2.0 ** -25, err

@@ -38,3 +38,16 @@ def test_bf16_products_get_a_tile_that_can_take_them():
                     seen.add((kind, v))
                     assert m > 16 and n >= 64 and k % (chunk[v - 1] * ks) == 0 and (kind != 3 or 3 <= v <= 5)
     assert {v for _, v in seen} == set(range(1, 8)) and {v for kd, v in seen if kd == 3} == {3, 4, 5}
+
+
+def test_small_fp32_products_get_waves_that_can_share_k():
+    L = rules.lib()
+    waves, seen = [8, 8, 4, 4], set()
+    for m, n, k, ks in itertools.product((1, 2, 17, 31, 32, 33, 64, 65, 128, 185, 256, 300, 700, 4096), (2, 4, 31, 64, 512, 1004, 2048, 4096, 32000),
+                                         (32, 64, 128, 192, 256, 320, 512, 576, 1024, 1088, 4096), (1, 2, 4, 8, 16)):
+        v = L.kwaves_variant(m, n, k, ks)
+        assert 0 <= v <= 4
+        if v:
+            seen.add(v)
+            assert n % 4 == 0 and k % (16 * waves[v - 1] * ks) == 0 and m * n * k <= 1.600001e9
+    assert seen == {1, 2, 3, 4}
