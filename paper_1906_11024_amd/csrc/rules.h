@@ -192,7 +192,8 @@ constexpr KwavesModel kTileModels[3] = {   // gemm_kernel, by gemm_tile_shape
     {64, 64, 0, 0.91f, 10.27f, 0.93f, 9.61f, 0.23f}, {64, 32, 0, 1.54f, 5.40f, 1.22f, 5.01f, 0.19f},
     {32, 32, 0, 1.17f, 3.68f, 1.29f, 3.25f, 0.09f}};
 constexpr float kKwavesMost = 1.6e9f;
-inline int gemm_kwaves_variant(int M, int N, int K, int ksplit) {
+// us: if given, the model's time for what is chosen
+inline int gemm_kwaves_variant(int M, int N, int K, int ksplit, float* us_out = nullptr) {
   if (M < 1 || N < 4 || N % 4 || K < 64 || ksplit < 1 || (float)M * (float)N * (float)K > kKwavesMost) return 0;
   if (M > 32 && N > 8 * K) return 0;
   auto us_of = [&](const KwavesModel& m) {
@@ -210,6 +211,7 @@ inline int gemm_kwaves_variant(int M, int N, int K, int ksplit) {
     const float us = us_of(m);
     if (us < best_us) { best_us = us; best = v; }
   }
+  if (us_out) *us_out = best_us;
   return best;
 }
 
@@ -234,6 +236,22 @@ inline int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain) {
   const long blocks = (long)((M + 63) / 64) * ((N + 63) / 64);
   // aim for >= 256 blocks (one per CU), keep at least 2 chunks of k per block
   while (blocks * ks < 256 && nchunks / (ks * 2) >= 2 && ks < 16) ks *= 2;
+  // A long k (the feed-forward's second product): gemm_kwaves.hip needs fewer splits, and its consumer adds fewer partials
+  // (LayerNorm of 185 rows over 16 4.9 us, over 4 4.5).  us, the split above / the one taken: 185 x 512 x 2048 8.3 (16) /
+  // 7.4 (2), 128 rows 5.9 (16) / 5.6 (4), 256 rows 8.5 (8) / 8.4 (2).  Products that are as wide as long gain nothing.
+  float best_us = 0.f;
+  if (dtype == 0 && !plain && M > 16 && K >= 2 * N) {
+    gemm_kwaves_variant(M, N, K, ks, &best_us);
+    const float partial = 2e-7f * (float)M * (float)N + 0.01f;
+    const int ks0 = ks;
+    best_us += (float)ks * partial;
+    for (int q = 1; q < ks0; q *= 2) {
+      float us = 0.f;
+      if (!gemm_kwaves_variant(M, N, K, q, &us)) continue;
+      us += (float)q * partial;
+      if (us < best_us) { best_us = us; ks = q; }
+    }
+  }
   return ks;
 }
 
