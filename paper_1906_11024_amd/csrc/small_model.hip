@@ -457,6 +457,12 @@ __global__ __launch_bounds__(kSmThreads) void small_decode_kernel(SmallDecode P)
         if (P.eos >= 0 && tok[r] == P.eos) {
           lp = j == 0 ? 0.f : -INFINITY;
           id = list % parts != 0 ? kNone : j == 0 ? P.eos : (j - 1 < P.eos ? j - 1 : j);
+        } else if (parts > 1 && !(fabsf(cum[r]) < 256.f)) {
+          // The parts hold more than the row's R best words.  The others must not win a tie by their lower index where the
+          // score before swallows what sets words apart: a dead row's -inf, or -1e9 (below 256 it keeps 2^-16).
+          int ahead = 0;
+          for (int i = r * parts * R; i < (r + 1) * parts * R; ++i) ahead += better(cand_v[i], cand_i[i], cand_v[list * R + j], id);
+          if (ahead >= R) id = kNone;
         }
         const float sc = cum[r] + lp;
         return id == kNone || !(sc == sc) ? Cand{-INFINITY, kNone} : Cand{sc, r * V + id};

@@ -445,6 +445,32 @@ def test_small_models_loop_equals_the_launches(eos, compact, beam):
         assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
 
 
+# Sentences whose scores so far are -inf, or so large that they swallow a word's: all words of a row tie, and the words that
+# count are the row's best ones, in the order of their numbers, as from the launches (debug = 2).
+@pytest.mark.parametrize("dead", [-np.inf, -1e9, 1e9])
+@pytest.mark.parametrize("beam,V", [(1, 1004), (2, 1004), (3, 260), (4, 1004), (5, 260), (8, 1004)])
+def test_small_models_take_the_best_words_of_dead_rows(beam, V, dead):
+    cfg = _cfg(batch=4, beam=beam, V=V)
+    assert rules.lib().small_model(cfg["d"], cfg["F"], V, cfg["n_dec"], beam, cfg["batch"])
+    w = wl.make_weights(cfg, seed=6, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(20.0)
+    src, lens = wl.make_source(cfg, 6)
+    rows, got = cfg["batch"] * beam, []
+    for debug in (0, 2):
+        gpu = hz.make_gpu(cfg, w, debug=debug)
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+        cum = torch.full((cfg["batch"], beam), dead, device="cuda")
+        cum[0, 0] = cum[1, beam - 1] = 0.0     # two sentences with a live row, in one of them behind its dead rows
+        cum = cum.reshape(-1).contiguous()
+        toks = torch.zeros(3, rows, dtype=torch.int32, device="cuda")
+        pars = torch.zeros_like(toks)
+        gpu.decode_n(3, tok, cum, toks, pars, torch.empty(rows, V, device="cuda"))
+        got.append([x.cpu().numpy() for x in (toks, pars)])
+        gpu.close()
+    assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][0], got[1][0])
+
+
 # bf16 products with their operands straight to LDS, every tile of them: (row counts, widths) whose products take it, rows and
 # columns that do not fill the last tile, q/k/v segments, fp32 partials split or not, ragged encoders, candidates, vocabularies
 # that end inside a tile.  Checked: a few sentences (a product's rows do not depend on each other), the last ones among them.
