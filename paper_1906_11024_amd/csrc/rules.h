@@ -127,12 +127,15 @@ inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragg
   if (M <= 16 || N < 64 || ksplit < 1 || K % (64 * ksplit)) return 0;
   const int k = K / ksplit;
   const bool cand = kind == 3;
-  if (ragged) M = M - M * 3 / 10;
   if (cand && (M <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
   if (ksplit > 1 && k < 1024) return 0;
   if (!cand && M <= 256 && k <= 512) return 0;   // 5 to 15 us of a 460 us pass over 16 sentences of up to 9 words
-  const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
+  long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   if (!cand && k >= 1024 && tiles64 <= 128) return 0;
+  // Up to here the padded rows decide, ragged or not: gemm_kernel may add its sums up in another order, and a batch without
+  // its padding has the bits of the padded one.  All tiles below add in the order of k.
+  if (ragged) M = M - M * 3 / 10;
+  tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   int best = 0;
   float best_us = 0.f;
   for (int v = 1; v <= kLdsVariants; ++v) {

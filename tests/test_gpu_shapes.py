@@ -229,7 +229,10 @@ def test_activations_too_large_to_split(value):
                                                                   ("f32", 6, 104, "A", None, 128, 4), ("bf16", 6, 104, "S", None, 128, 4),
                                                                   ("f32", 5, 130, "A", [2, 1], 128, 4),
                                                                   # rows wider than the LayerNorm of one wave takes
-                                                                  ("f32", 18, 61, "A", None, 576, 9), ("bf16", 18, 61, "A", None, 640, 20)])
+                                                                  ("f32", 18, 61, "A", None, 576, 9), ("bf16", 18, 61, "A", None, 640, 20),
+                                                                  # a follower's value product of 610 padded rows and 427 without
+                                                                  # padding: on both sides of gemm_lds_variant's line for k >= 1024
+                                                                  ("bf16", 10, 61, "A", [2, 1], 1024, 32)])
 def test_ragged_encoder_equals_the_padded_one(dtype, batch, max_src, share, enc_pi, d, H):
     """Lengths 0 .. max_src.  The rows of a product or a LayerNorm do not depend on each other, so leaving out the
     padding changes no bit (debug = 1 keeps the padded route); a few sentences are checked against the oracle."""

@@ -40,6 +40,14 @@ def test_bf16_products_get_a_tile_that_can_take_them():
     assert {v for _, v in seen} == set(range(1, 8)) and {v for kd, v in seen if kd == 3} == {3, 4, 5}
 
 
+def test_padding_does_not_choose_the_kernel_of_a_bf16_product():
+    """A ragged batch has the bits of the padded one: gemm_kernel, which may add up in another order, takes both or neither."""
+    L = rules.lib()
+    for m, n, k, kind in itertools.product((*range(512, 1500, 20), 2440, 4500, 9000), (64, 128, 512, 1024, 1088, 2048, 3072), (64, 512, 1024, 2048, 4096), (0, 2)):
+        for ks in {1, L.pick_ksplit(m, n, k, 1)} if kind == 2 else {1}:
+            assert (L.lds_variant(m, n, k, kind, ks, 1) == 0) == (L.lds_variant(m, n, k, kind, ks, 0) == 0), (m, n, k, kind, ks)
+
+
 def test_small_fp32_products_get_waves_that_can_share_k():
     L = rules.lib()
     waves, seen = [8, 8, 4, 4], set()
