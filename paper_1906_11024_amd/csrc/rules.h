@@ -129,7 +129,9 @@ inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragg
   const bool cand = kind == 3;
   if (cand && (M <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
   if (ksplit > 1 && k < 1024) return 0;
-  if (!cand && M <= 256 && k <= 512) return 0;   // 5 to 15 us of a 460 us pass over 16 sentences of up to 9 words
+  // 5 to 15 us of a 460 us pass over 16 sentences of up to 9 words.  Not output layers: gemm_kernel has no large tile in bf16
+  // (128 x 32000 x 512 with its logits 17.9 / 13.6, 256 rows 27.7 / 16.7; a 128 x 128 tile of it took 15.1 and 20.1).
+  if (!cand && M <= 256 && k <= 512 && (M < 128 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
   long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   if (!cand && k >= 1024 && tiles64 <= 128) return 0;
   // Up to here the padded rows decide, ragged or not: gemm_kernel may add its sums up in another order, and a batch without

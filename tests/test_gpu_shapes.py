@@ -485,6 +485,7 @@ _LDS = {   # case: (variant, (M, N, K, kind, k split, ragged) of the product mea
     "192x128_ragged": (4, (15250, 512, 512, 2, 1, 1), dict(batch=250, d=512, H=8, F=192, src_len=(1, 61), steps=1)),
     "256x256": (5, (9150, 2048, 512, 0, 1, 1), dict(batch=150, d=512, H=8, F=2048, src_len=(1, 61), steps=1)),
     "320x256": (6, (7930, 3072, 1024, 0, 1, 1), dict(batch=130, d=1024, H=16, F=128, src_len=(1, 61), steps=1)),
+    "128x128_logits": (4, (185, 32004, 512, 1, 1, 0), dict(batch=185, d=512, H=8, V=32004, src_len=(1, 2))),
     "128x128_candidates": (3, (68, 32004, 512, 3, 1, 0), dict(batch=17, beam=4, d=512, H=8, V=32004)),
     "192x128_candidates": (4, (300, 32004, 512, 3, 1, 0), dict(batch=75, beam=4, d=512, H=8, V=32004, src_len=(1, 2))),
     "256x256_candidates": (5, (500, 32004, 512, 3, 1, 0), dict(batch=125, beam=4, d=512, H=8, V=32004, src_len=(1, 2))),

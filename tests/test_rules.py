@@ -37,6 +37,8 @@ def test_bf16_products_get_a_tile_that_can_take_them():
                 if v:
                     seen.add((kind, v))
                     assert m > 16 and n >= 64 and k % (chunk[v - 1] * ks) == 0 and (kind != 3 or 3 <= v <= 5)
+    # output layers of 128 to 256 rows are no small products: gemm_kernel has no large tile in bf16
+    assert all(L.lds_variant(m, 32000, 512, 1, 1, 0) for m in (128, 185, 256)) and not L.lds_variant(256, 2048, 512, 0, 1, 0)
     assert {v for _, v in seen} == set(range(1, 8)) and {v for kd, v in seen if kd == 3} == {3, 4, 5}
 
 
