@@ -199,6 +199,9 @@ template <int LPP> __device__ __forceinline__ float lanes_sum(float v) {
   return sum_xor16(group_sum<16>(v));
 }
 
+// four fp32 values on any 4-byte boundary: a global access of 16 bytes needs no more, and is one instruction
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // 16 bytes per lane from base + off (bytes) straight to LDS at lds + 16 * lane (lds: byte offset, uniform).  Counted by
 // vmcnt like any load; the compiler does not know of it, so the waits stand in the kernel.
 __device__ __forceinline__ void load_to_lds(const void* base, unsigned off, unsigned lds) {

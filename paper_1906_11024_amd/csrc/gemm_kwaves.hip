@@ -217,7 +217,7 @@ __global__ __launch_bounds__(KW * 64) void kwaves_kernel(GemmParams p) {
       dst = reinterpret_cast<float*>(s == 0 ? p.out[0] : (s == 1 ? p.out[1] : p.out[2])) + (size_t)t_step * ts +
             (size_t)m * (s == 0 ? p.ldo[0] : (s == 1 ? p.ldo[1] : p.ldo[2])) + (col - s * p.seg_w);
     }
-    *reinterpret_cast<f32x4*>(dst) = v;
+    *reinterpret_cast<f32x4_any*>(dst) = v;
   }
   if (p.bump && tile_x == 0 && tile_y == 0 && blockIdx.y == 0 && tid == 0) *p.bump = *p.bump + 1;
 }

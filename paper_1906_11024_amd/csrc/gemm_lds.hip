@@ -28,6 +28,7 @@ namespace san {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // WM x WN waves, each TM x TN tiles of 32 x 32; k in chunks of BK, ST chunks of LDS.
 template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND>
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
         constexpr int PC = BN / 4;
         for (int q = tid; q < PR * PC; q += NT) {
           const int r = q / PC, n = n0 + (q % PC) * 4, i = i0 + r / 32 % TP, m = m0 + (r / 32 / TP * TM + i) * 32 + r % 32;
-          if (i < TM && m < p.M && n < p.N) *reinterpret_cast<float4*>(base + (size_t)m * ld + n) = *reinterpret_cast<const float4*>(tile + r * LDW + (q % PC) * 4);
+          if (i < TM && m < p.M && n < p.N) *reinterpret_cast<f32x4_any*>(base + (size_t)m * ld + n) = *reinterpret_cast<const f32x4*>(tile + r * LDW + (q % PC) * 4);
         }
       }
     }

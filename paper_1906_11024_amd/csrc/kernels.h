@@ -55,26 +55,25 @@ hipError_t launch_gemm_split(const GemmParams& p, int wm, hipStream_t stream);
 hipError_t launch_check_splittable(const float* w, size_t n, int* flag, hipStream_t stream);
 
 // bf16 only: the same product with its operands straight to LDS (gemm_lds.hip); variant: gemm_lds_variant.  launch_gemm
-// takes it by itself where that says so.  It loads and stores 16 bytes at a time: gemm_lds_aligned (the logits go where the
-// caller wants them, every other operand is the library's own and aligned).
+// takes it by itself where that says so.  It loads and stores 16 bytes at a time, in fp32 outputs on any 4-byte boundary (the
+// logits go where the caller wants them, every other operand is the library's own and aligned).
 inline bool gemm_lds_aligned(const GemmParams& p) {
   auto at16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
   if (!at16(p.A) || !at16(p.W) || p.lda % 8 || (p.bias && reinterpret_cast<uintptr_t>(p.bias) % 8)) return false;
   if (p.out_kind == 3) return true;
-  const int per = p.out_kind == 0 ? 8 : 4;
+  if (p.out_kind != 0) return p.N % 4 == 0 && p.seg_w >= p.N;
   for (int i = 0; i < 3; ++i)
-    if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % per || p.tstride[i] % per)) return false;
-  return p.N % per == 0 && (p.seg_w >= p.N || (p.out_kind == 0 && p.seg_w % per == 0));
+    if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % 8 || p.tstride[i] % 8)) return false;
+  return p.N % 8 == 0 && (p.seg_w >= p.N || p.seg_w % 8 == 0);
 }
 hipError_t launch_gemm_lds(const GemmParams& p, int variant, hipStream_t stream);
 
 // fp32 only: small products through bf16 parts with k dealt to the waves of a block (gemm_kwaves.hip); variant:
-// gemm_kwaves_variant.  launch_gemm takes it by itself where that says so, unless `plain` is set.  16 bytes at a time.
+// gemm_kwaves_variant.  launch_gemm takes it by itself where that says so, unless `plain` is set.  16 bytes at a time, to
+// outputs on any 4-byte boundary.
 inline bool gemm_kwaves_aligned(const GemmParams& p) {
   auto at16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
   if (!at16(p.A) || !at16(p.W) || p.lda % 4 || (p.bias && !at16(p.bias))) return false;
-  for (int i = 0; i < 3; ++i)
-    if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % 4 || p.tstride[i] % 4)) return false;
   return p.N % 4 == 0 && (p.seg_w >= p.N || p.seg_w % 4 == 0);
 }
 hipError_t launch_gemm_kwaves(const GemmParams& p, int variant, hipStream_t stream);

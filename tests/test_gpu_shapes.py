@@ -512,7 +512,7 @@ def test_bf16_products_straight_to_lds_match_oracle(case):
     gpu.close()
 
 
-# The logits may lie on any 4-byte boundary: no 16-byte stores there.  The same sums in either kernel, up to their order.
+# The logits may lie on any 4-byte boundary.
 @pytest.mark.parametrize("rows", [40, 300])
 def test_bf16_logits_on_a_4_byte_boundary(rows):
     cfg = _cfg(dtype="bf16", batch=rows, d=512, H=8, F=192, V=16004, src_len=(1, 2))
@@ -553,8 +553,7 @@ def test_fp32_products_dealt_to_waves_match_oracle(case):
     ls.gpu.close()
 
 
-# Logits on any 4-byte boundary: no 16-byte stores there, and the fp32 instructions round otherwise (2^-24 of the products'
-# absolute sum at most once per k-value; here 512 of them, of random signs).
+# The same in fp32.
 def test_fp32_logits_on_a_4_byte_boundary():
     rows = 40
     cfg = _cfg(batch=rows, d=512, H=8, F=64)
@@ -570,6 +569,28 @@ def test_fp32_logits_on_a_4_byte_boundary():
     a, b = buf[0, :rows * cfg["V"]].cpu().numpy(), buf[1, 1:1 + rows * cfg["V"]].cpu().numpy()
     assert buf[1, 0] == 0 and (buf[1, 1 + rows * cfg["V"]:] == 0).all()
     assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max()
+    gpu.close()
+
+
+# Where the logits lie changes no bit of them, and no neighbour: output layers of every kernel, last column tiles with 4 live
+# columns.
+@pytest.mark.parametrize("dtype,rows,V", [("f32", 4, 1004), ("f32", 40, 1004), ("f32", 185, 25604), ("bf16", 40, 1004), ("bf16", 300, 1004),
+                                          ("bf16", 256, 25604)])
+def test_logits_do_not_depend_on_where_they_lie(dtype, rows, V):
+    cfg = _cfg(dtype=dtype, batch=rows, d=512, H=8, F=64, V=V, src_len=(1, 2))
+    w = wl.make_weights(cfg, seed=3)
+    src, lens = wl.make_source(cfg, 3)
+    gpu = hz.make_gpu(cfg, w)
+    buf = torch.zeros(4, rows * V + 4, device="cuda")
+    tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+    for i in range(4):
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        gpu.decode_step(tok, buf[i, i:i + rows * V].view(rows, V))
+    got = buf.cpu().numpy()
+    assert got[0, :rows * V].any()
+    for i in range(4):
+        assert np.array_equal(got[i, i:i + rows * V], got[0, :rows * V]), i
+        assert not got[i, :i].any() and not got[i, i + rows * V:].any()
     gpu.close()
 
 
