@@ -85,18 +85,30 @@ inline bool few_rows_faster(int dtype, int rows, int d) {
 
 // Models whose decoder steps run with one workgroup per sentence (small_model.hip), and whether they do for `batch`
 // sentences.  A model of both routes, in us a step of R = beam rows a sentence and L layers, with MB the weights a step
-// reads, all of them by one workgroup:
-//   one workgroup a sentence   6 + 6.2 L + (5 + 4 R) MB for every 256 sentences
-//   launches                   21 + 27 L
+// reads, all of them by one workgroup, and keys the positions that its attentions read (2 a position for a head, which reads
+// keys and values, 1 for a follower):
+//   one workgroup a sentence   6 + 6.2 L + (5 + 4 R) MB + p keys for every 256 sentences
+//   launches                   21 + 27 L + 0.006 keys
+// p = d / H times the larger of 3e-4 + 4e-5 R H and 7e-5 R H (8 waves deal with the R H pairs of rows and heads), 1.4 times that
+// where 32 sentences or more want their caches at once; the launches' attention has the whole chip.
 // Measured (us, launches / one workgroup): 64 columns, F 256, 2 layers, 1000 words (0.7 MB) beam 1 70 / 21, 4 73 / 32,
 // 8 78 / 44, 300 sentences of beam 1 79 / 42; 6 layers (1.6 MB) beam 4 182 / 76; 4000 words (1.5 MB) beam 4 74 / 48;
 // 128 columns, F 512, 2 layers, 1000 words (2.3 MB) beam 1 72 / 35, 4 77 / 59; 6 layers, 2004 words (6.5 MB) beam 1
-// 190 / 111, 4 192 / 175, 8 196 / 240.  The line leaves 15 % to the launches.
+// 190 / 111, 4 192 / 175, 8 196 / 240.  The line leaves 15 % to the launches.  With positions (2 and 64 sentences, 2 layers of
+// 64 columns, 4 heads, means of a decode): 512 target positions beam 1 77 / 28 and 84 / 30, beam 8 84 / 89 and 99 / 106; 1024
+// source positions beam 1 85 / 36 and 98 / 50, beam 4 78 / 79 and 100 / 93, beam 8 82 / 140 and 130 / 155; 1024 of both beam 1
+// 96 / 50 and 112 / 74.  Of 586 such settings (1 to 8 heads, 16 to 1024 positions) none is more than 3 % slower than with the
+// launches, 45 stay with them that would gain 10 % or more: here 8 % are left.
 constexpr int kSmallLds = 160 * 1024, kSmallBeam = 8;   // LDS of a workgroup; its search sorts the candidates of this beam at once
-inline bool small_model_faster(int d, int F, int V, int layers, int beam, int batch) {
+inline bool small_model_faster(int d, int F, int V, int layers, int beam, int batch, int H = 1, float keys = 0.f) {
   if ((d != 64 && d != 128) || (F != 64 && F != 128 && F != 256 && F != 512) || beam < 1 || beam > kSmallBeam || batch < 1) return false;
   const float mb = 4e-6f * ((float)layers * (6.f * d * d + 2.f * d * F) + (float)V * d);
-  return (float)((batch + 255) / 256) * (6.f + 6.2f * layers + (5.f + 4.f * beam) * mb) <= 0.85f * (21.f + 27.f * layers);
+  const float rounds = (float)((batch + 255) / 256), launches = 21.f + 27.f * layers;
+  const float here = rounds * (6.f + 6.2f * layers + (5.f + 4.f * beam) * mb);
+  if (here > 0.85f * launches) return false;
+  const float rh = (float)(beam * H), few = 3e-4f + 4e-5f * rh, many = 7e-5f * rh;
+  const float p = (float)(d / H) * (few > many ? few : many) * (batch >= 32 ? 1.4f : 1.f);
+  return here + rounds * p * keys <= 0.92f * (launches + 0.006f * keys);
 }
 
 // bf16 products with their operands straight to LDS (gemm_lds.hip): which tile, or 0 for gemm_kernel.  kind: GemmParams::

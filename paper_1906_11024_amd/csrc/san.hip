@@ -113,6 +113,7 @@ struct san_ctx {
   float* part = nullptr;
   size_t part_elems = 0;
   SmallLayer* small_layers = nullptr;   // models whose steps can run in one launch (small_model.hip); null: not this one
+  int small_self = 0, small_ctx = 0;    // what its attentions read of a target and of a source position (keys of small_model_faster)
   float* aan_all = nullptr;   // AAN running sums [layer][rows_max][d]
   float* dbg_enc = nullptr;   // debug copy of the encoder output [batch*max_src][d]
   // policy learning: running JS sums [2][L][L] (self, enc-dec), per-pair scratch, sample counts
@@ -623,6 +624,8 @@ static int build_ctx(san_ctx* c, const Blob& bl, const void* blob, const std::ve
         o.dbg_A_self = L.dbg_A_self; o.dbg_A_ctx = L.dbg_A_ctx; o.dbg_hidden = L.dbg_hidden;
         o.S_self = self_shared || dbg ? c->dec[L.self_head].S_self : nullptr;
         o.S_ctx = ctx_shared || (dbg && o.ctx_head) ? Hd.S_ctx : nullptr;
+        c->small_self += o.self_head ? 2 : 1;
+        c->small_ctx += o.ctx_head ? 2 : shareS ? 1 : 0;
         o.mem_k = f(L.mem);
         o.mem_v = o.ctx_head ? f(L.mem) + d : f(L.mem);
       }
@@ -1190,10 +1193,11 @@ static SmallDecode small_decode(const san_ctx* c) {
   p.eos = c->cfg.eos_id; p.done = c->done_dev; p.done_count = c->done_dev + c->cfg.max_batch;
   return p;
 }
-// Whether steps run there (san_profile times the launches of the general route)
-static bool small_route(const san_ctx* c, bool search) {
+// Whether steps run there that see `positions` target positions on average (san_profile times the launches of the general route)
+static bool small_route(const san_ctx* c, bool search, int positions) {
   if (!c->small_layers || c->prof_on ||
-      !small_model_faster(c->d, c->F, c->V, (int)c->dec.size(), c->cfg.beam, c->batch))
+      !small_model_faster(c->d, c->F, c->V, (int)c->dec.size(), c->cfg.beam, c->batch, c->H,
+                          (float)c->small_self * (float)positions + (float)c->small_ctx * (float)c->max_src))
     return false;
   SmallDecode p = small_decode(c);
   if (!search) p.logits = (float*)1;   // only whether it is there counts
@@ -1206,7 +1210,7 @@ static int decode_step_impl(san_ctx* c, const int32_t* tokens_dev, float* logits
   if (c->t < 0) return fail(c, SAN_ESTATE, "san_decode_step before san_encode");
   if (c->t >= c->cfg.max_tgt_len) return fail(c, SAN_ECAPACITY, "san_decode_step: max_tgt_len steps already decoded");
   c->launches = 0;
-  if (!skip_embed && c->cand_tiles == 0 && small_route(c, false)) {
+  if (!skip_embed && c->cand_tiles == 0 && small_route(c, false, c->t + 1)) {
     SmallDecode p = small_decode(c);
     p.tok_in = tokens_dev;
     p.logits = logits_dev;
@@ -1538,7 +1542,7 @@ int san_decode_n(san_ctx* c, int32_t n, const int32_t* tokens_dev, float* cum_io
       if ((rc = dalloc(c, (void**)&c->part_ms, slots * 2 * 4, false))) return rc;   // last: it switches the mode on
     }
   }
-  const bool small = !(flags & SAN_LOOP_LOGITS) && small_route(c, true);
+  const bool small = !(flags & SAN_LOOP_LOGITS) && small_route(c, true, c->t + (n + 1) / 2);
   if (!small) {
   HIP_TRY(c, hipMemcpyAsync(c->pp_tok[0], tokens_dev, (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->pp_cum[0], cum_io_dev, (size_t)rows0 * 4, hipMemcpyDeviceToDevice, c->stream));

@@ -13,6 +13,7 @@ extern "C" int split_ks(int M, int N, int K, int ks_min, int ks_max) { return sa
 extern "C" int few_rows(int dtype, int rows, int d) { return san::few_rows_faster(dtype, rows, d); }
 extern "C" int skinny(int dtype, int M, int N, int K, int kind, int ks) { return san::gemm_skinny_faster(dtype, M, N, K, kind, ks); }
 extern "C" int small_model(int d, int F, int V, int layers, int beam, int batch) { return san::small_model_faster(d, F, V, layers, beam, batch); }
+extern "C" int small_model_at(int d, int F, int V, int layers, int beam, int batch, int H, int keys) { return san::small_model_faster(d, F, V, layers, beam, batch, H, (float)keys); }
 extern "C" int lds_variant(int M, int N, int K, int kind, int ks, int ragged) { return san::gemm_lds_variant(M, N, K, kind, ks, ragged != 0); }
 extern "C" int kwaves_variant(int M, int N, int K, int ks) { return san::gemm_kwaves_variant(M, N, K, ks); }
 extern "C" int cand_n(int N) { return san::gemm_skinny_cand_n(N); }

@@ -448,6 +448,25 @@ def test_small_models_loop_equals_the_launches(eos, compact, beam):
         assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
 
 
+# The rule counts the positions that are read: a decode goes from one launch a step to the launches of the general route.
+@pytest.mark.parametrize("loop", [None, "cands"])
+@pytest.mark.parametrize("beam,H,src", [(8, 4, 420), (4, 1, 612)])
+def test_small_models_hand_over_to_the_launches(beam, H, src, loop):
+    cfg = _cfg(batch=3, beam=beam, H=H, F=64, V=260, src_len=(src // 2, src), steps=12)
+    here = [rules.lib().small_model_at(64, 64, 260, 3, beam, 3, H, 5 * (t + 1) + 4 * src) for t in range(12)]
+    assert here == [1] * 8 + [0] * 4
+    w = wl.make_weights(cfg, seed=31, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(8.0)
+    src_ids, lens = wl.make_source(cfg, 31)
+    gpu = hz.make_gpu(cfg, w)
+    ls = hz.Lockstep(gpu, hz.make_oracle(cfg, w), src_ids, lens, beam, loop=loop)
+    for one in here:
+        ls.step(logit_tol=F32_TOL)
+        assert loop or (gpu.last_launch_count == 1) == one
+    assert loop or max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
+    gpu.close()
+
+
 # Sentences whose scores so far are -inf, or so large that they swallow a word's: all words of a row tie, and the words that
 # count are the row's best ones, in the order of their numbers, as from the launches (debug = 2).
 @pytest.mark.parametrize("dead", [-np.inf, -1e9, 1e9])

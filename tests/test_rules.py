@@ -61,3 +61,14 @@ def test_small_fp32_products_get_waves_that_can_share_k():
             seen.add(v)
             assert n % 4 == 0 and k % (16 * waves[v - 1] * ks) == 0 and m * n * k <= 1.600001e9
     assert seen == {1, 2, 3, 4}
+
+
+def test_small_models_leave_long_histories_to_the_launches():
+    """Measured (us, launches / one workgroup a sentence): 77 / 28, 84 / 30, 84 / 89, 99 / 106, 82 / 140, 130 / 155; 89 / 58, 139 / 153."""
+    L = rules.lib()
+    for want, d, F, beam, batch, H, keys in ((1, 64, 256, 1, 2, 4, 800), (1, 64, 256, 1, 64, 4, 800), (0, 64, 256, 8, 2, 4, 800), (0, 64, 256, 8, 64, 4, 800),
+                                             (0, 64, 256, 8, 2, 4, 2072), (0, 64, 256, 8, 64, 4, 2072), (1, 128, 512, 1, 2, 2, 800), (0, 128, 512, 1, 256, 2, 1568)):
+        assert L.small_model_at(d, F, 1000, 2, beam, batch, H, keys) == want, (d, beam, batch, keys)
+    for beam, batch, H in itertools.product((1, 3, 8), (1, 31, 32, 300), (1, 2, 4)):
+        here = [L.small_model_at(64, 128, 1000, 3, beam, batch, H, keys) for keys in range(0, 9000, 50)]
+        assert here == sorted(here, reverse=True) and here[0] == L.small_model(64, 128, 1000, 3, beam, batch)
