@@ -414,7 +414,7 @@ static hipError_t launch_gemm_cand(int dtype, const GemmParams& p, bool plain, h
     return hipErrorInvalidValue;
   const int tile = cand_pick_tile(p.M, p.N, p.K, dtype);
   if (dtype == 1) {
-    if (const int v = gemm_lds_variant(p.M, p.N, p.K, 3, 1, false)) return launch_gemm_lds(p, v, stream);
+    if (const int v = gemm_lds_variant(p.M, p.N, p.K, 3, 1, false)) return launch_gemm_lds(p, v, 1, stream);
     if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256, true>(p, stream);
     if (p.K % 128 == 0) return launch_tile<bf16_t, 2, 2, 1, 1, 1, 2, 256, true>(p, stream);
     return launch_tile<bf16_t, 2, 2, 1, 1, 1, 4, 128, true>(p, stream);
@@ -445,7 +445,8 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
       if (const int v = gemm_kwaves_variant(p.M, p.N, p.K, p.ksplit)) return launch_gemm_kwaves(p, v, stream);
   }
   if (dtype == 1 && gemm_lds_aligned(p))
-    if (const int v = gemm_lds_variant(p.M, p.N, p.K, p.out_kind, p.ksplit, (p.flags & kGemmRagged) != 0)) return launch_gemm_lds(p, v, stream);
+    if (const int v = gemm_lds_variant(p.M, p.N, p.K, p.out_kind, p.ksplit, (p.flags & kGemmRagged) != 0))
+      return launch_gemm_lds(p, v, gemm_k_groups(p.M, p.N, p.K, p.ksplit, p.out_kind == 2), stream);
   int tile = gemm_pick_tile(p.M, p.N, p.K, dtype, p.out_kind == 2);
   if (p.ksplit > 1 && tile != 3) tile = 0;   // only the small tiles split k across blocks
   const int chunks = (p.K / (dtype == 1 ? 64 : 32) + p.ksplit - 1) / p.ksplit;   // in 128-byte units

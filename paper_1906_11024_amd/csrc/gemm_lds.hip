@@ -11,6 +11,8 @@
 // The weights are the A operand, so that a lane holds four neighbouring columns of one row: the tile goes through LDS in
 // 8- and 16-byte writes and leaves in whole lines (2-byte stores of 64-byte pieces took 3 us of a 64 x 128 tile).
 // Every XCD takes a run of neighbouring tiles, of rows or columns as the larger operand asks.
+// Sums have the bits of gemm_kernel's, which deals small products to groups of waves: the 64 x 64 tiles keep as many sums per
+// output (a decode of 300 to 1020 rows is within 1 % of one sum's time; with those products left to gemm_kernel up to 8 % slower).
 // Measured (us, gemm_kernel / here; K in the middle of the encoder's and the decoder's): 8900 x 2048 x 512 48.8 / 24.8,
 // x 1536 x 512 46.8 / 22.2, x 512 x 2048 (fp32 out) 54 / 30, x 512 x 512 20.3 / 12.7; 12300 x 3072 x 1024 144 / 86, x 1024 x 4096
 // 156 / 112 (0.93 PFLOP/s; rates of 1.3 where the tiles fill the chip); 1024 x 2048 x 512 7.5 / 6.7, 512 x 4096 x 1024
@@ -30,8 +32,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// WM x WN waves, each TM x TN tiles of 32 x 32; k in chunks of BK, ST chunks of LDS.
-template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND>
+// WM x WN waves, each TM x TN tiles of 32 x 32; k in chunks of BK, ST chunks of LDS.  G sums per output, CU chunks to each in
+// turn, added up in order at the end: what gemm_kernel does with its groups of waves, bit for bit (gemm_k_groups).
+template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND, int G, int CU>
 __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
   constexpr int NW = WM * WN, NT = NW * 64;
   constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
@@ -87,7 +90,16 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
 
   // The weights are the MFMA's A operand: acc[i][j][v] is row (wm TM + i) 32 + l32 and column (wn TN + j) 32 + (v / 4) 8 +
   // kh 4 + v % 4, so that a lane holds four neighbouring columns and the tile goes to LDS in wide writes
-  f32x16 acc[TM][TN];
+  f32x16 accs[G][TM][TN];
+  auto& acc = accs[0];
+#pragma unroll
+  for (int g = 1; g < G; ++g)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) accs[g][i][j][v] = 0.f;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     float bv[16];
@@ -119,11 +131,11 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) wf[set][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wr + at + j * 32 * RB));
   };
-  auto multiply = [&](int set) {
+  auto multiply = [&](int set, int g) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][j], xf[set][i], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < TN; ++j) accs[g][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][j], xf[set][i], accs[g][i][j], 0, 0, 0);
   };
   // the reads of the next step go between the MFMAs of this one
   auto interleave = [&] {
@@ -146,11 +158,11 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
   arrive(0);
   if (ST - 1 < nch) fetch(ST - 1, ST - 1);
   read(0, piece(0, 0));
-  for (int c = 0; c < nch; ++c) {
+  auto chunk = [&](int c, int g) {
 #pragma unroll
     for (int s = 0; s < STEPS - 1; ++s) {
       read((s + 1) & 1, piece(c, s + 1));
-      multiply(s & 1);
+      multiply(s & 1, g);
       interleave();
     }
     // all of the chunk is in registers: its LDS is free, and the last step covers the first reads of the next chunk
@@ -159,9 +171,22 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
       if (c + ST < nch) fetch(c + ST, c % ST);
       read(0, piece(c + 1, 0));
     }
-    multiply((STEPS - 1) & 1);
+    multiply((STEPS - 1) & 1, g);
     interleave();
+  };
+  for (int c = 0; c < nch; c += G * CU) {
+#pragma unroll
+    for (int u = 0; u < G * CU; ++u)
+      if (u == 0 || c + u < nch) chunk(c + u, u / CU);
   }
+#pragma unroll
+  for (int g = 1; g < G; ++g)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] += accs[g][i][j][v];
   __syncthreads();   // the stages are dead
 
   if (!CAND && p.out_kind == 0) {
@@ -238,7 +263,7 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
   if (p.bump && tile_x == 0 && tile_y == 0 && tid == 0) *p.bump = *p.bump + 1;
 }
 
-template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND>
+template <int WM, int WN, int TM, int TN, int BK, int ST, bool CAND, int G = 1, int CU = 1>
 static hipError_t launch_lds_t(const GemmParams& p, hipStream_t stream) {
   constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
   constexpr int TP = TM < 3 ? TM : 2, full = BM * (BN * 2 + 16), half = full <= 160 * 1024 ? full : full / 2;
@@ -252,14 +277,14 @@ static hipError_t launch_lds_t(const GemmParams& p, hipStream_t stream) {
   if (e != hipSuccess) return e;
   const unsigned long long bit = 1ull << (dev & 63);
   if (!(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lds_kernel<WM, WN, TM, TN, BK, ST, CAND>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lds_kernel<WM, WN, TM, TN, BK, ST, CAND, G, CU>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     raised.fetch_or(bit, std::memory_order_release);
   }
   GemmParams q = p;
   q.xcd_rows = p.N > p.M;   // tiles run down the columns of the larger operand
   const long tiles = (long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-  hipLaunchKernelGGL((lds_kernel<WM, WN, TM, TN, BK, ST, CAND>), dim3((unsigned)((tiles + 7) / 8 * 8), p.ksplit), dim3(WM * WN * 64), smem, stream, q);
+  hipLaunchKernelGGL((lds_kernel<WM, WN, TM, TN, BK, ST, CAND, G, CU>), dim3((unsigned)((tiles + 7) / 8 * 8), p.ksplit), dim3(WM * WN * 64), smem, stream, q);
   return hipGetLastError();
 }
 
@@ -270,13 +295,22 @@ template <int TM, bool CAND> static hipError_t launch_lds_128(const GemmParams& 
   return tiles <= 256 ? launch_lds_t<2, 4, TM, 1, 64, 3, CAND>(p, stream) : launch_lds_t<2, 4, TM, 1, 64, 2, CAND>(p, stream);
 }
 
-hipError_t launch_gemm_lds(const GemmParams& p, int variant, hipStream_t stream) {
+// 64 x 64 tiles; a group's turn is 128 values of k where K is a multiple of it, else 64
+template <int BK, int ST> static hipError_t launch_lds_64(const GemmParams& p, int groups, hipStream_t stream) {
+  if (groups == 1) return launch_lds_t<2, 2, 1, 1, BK, ST, false>(p, stream);
+  if (BK == 64 && p.K % 128 == 0)
+    return groups == 2 ? launch_lds_t<2, 2, 1, 1, BK, ST, false, 2, 128 / BK>(p, stream) : launch_lds_t<2, 2, 1, 1, BK, ST, false, 4, 128 / BK>(p, stream);
+  return groups == 2 ? launch_lds_t<2, 2, 1, 1, BK, ST, false, 2>(p, stream) : launch_lds_t<2, 2, 1, 1, BK, ST, false, 4>(p, stream);
+}
+
+hipError_t launch_gemm_lds(const GemmParams& p, int variant, int groups, hipStream_t stream) {
   if (p.M < 1 || p.N < 4 || p.N % 4 || p.ksplit < 1 || (p.ksplit > 1 && p.out_kind != 2) || !gemm_lds_aligned(p)) return hipErrorInvalidValue;
   const bool cand = p.out_kind == 3;
   if (cand && (variant < 3 || variant > 5)) return hipErrorInvalidValue;
+  if (groups != 1 && ((groups != 2 && groups != 4) || (variant != 1 && variant != 2))) return hipErrorInvalidValue;
   switch (variant) {
-    case 1: return launch_lds_t<2, 2, 1, 1, 128, 2, false>(p, stream);
-    case 2: return launch_lds_t<2, 2, 1, 1, 64, 4, false>(p, stream);
+    case 1: return launch_lds_64<128, 2>(p, groups, stream);
+    case 2: return launch_lds_64<64, 4>(p, groups, stream);
     case 3: return cand ? launch_lds_128<2, true>(p, stream) : launch_lds_128<2, false>(p, stream);
     case 4: return cand ? launch_lds_128<3, true>(p, stream) : launch_lds_128<3, false>(p, stream);
     case 5: return cand ? launch_lds_t<2, 4, 4, 2, 64, 2, true>(p, stream) : launch_lds_t<2, 4, 4, 2, 64, 2, false>(p, stream);

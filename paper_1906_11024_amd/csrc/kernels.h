@@ -54,7 +54,7 @@ hipError_t launch_gemm_split(const GemmParams& p, int wm, hipStream_t stream);
 // *flag = 1 if one of the n fp32 parameters is 2^16 or larger, or not finite (gemm_split.hip cannot take the model)
 hipError_t launch_check_splittable(const float* w, size_t n, int* flag, hipStream_t stream);
 
-// bf16 only: the same product with its operands straight to LDS (gemm_lds.hip); variant: gemm_lds_variant.  launch_gemm
+// bf16 only: the same product with its operands straight to LDS (gemm_lds.hip); variant: gemm_lds_variant, groups: gemm_k_groups.  launch_gemm
 // takes it by itself where that says so.  It loads and stores 16 bytes at a time, in fp32 outputs on any 4-byte boundary (the
 // logits go where the caller wants them, every other operand is the library's own and aligned).
 inline bool gemm_lds_aligned(const GemmParams& p) {
@@ -66,7 +66,7 @@ inline bool gemm_lds_aligned(const GemmParams& p) {
     if (p.out[i] && (!at16(p.out[i]) || p.ldo[i] % 8 || p.tstride[i] % 8)) return false;
   return p.N % 8 == 0 && (p.seg_w >= p.N || p.seg_w % 8 == 0);
 }
-hipError_t launch_gemm_lds(const GemmParams& p, int variant, hipStream_t stream);
+hipError_t launch_gemm_lds(const GemmParams& p, int variant, int groups, hipStream_t stream);
 
 // fp32 only: small products through bf16 parts with k dealt to the waves of a block (gemm_kwaves.hip); variant:
 // gemm_kwaves_variant.  launch_gemm takes it by itself where that says so, unless `plain` is set.  16 bytes at a time, to

@@ -135,8 +135,10 @@ constexpr LdsModel kLdsModels[kLdsVariants] = {
     {128, 64, 1.90f, 2.30f, 2.00f, 2.30f, 0.1f}};
 constexpr LdsModel kLdsCandModels[3] = {   // of 3, 4 and 5
     {128, 128, 0.8f, 9.6f, 1.0f, 5.0f, 0.3f}, {192, 128, 2.5f, 10.f, 2.7f, 5.8f, 0.2f}, {256, 256, 12.7f, 13.4f, 12.7f, 13.4f, 0.f}};
+inline int gemm_k_groups(int M, int N, int K, int ksplit, bool partials);
 inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragged) {
   if (M <= 16 || N < 64 || ksplit < 1 || K % (64 * ksplit)) return 0;
+  if (K % 128 == 0 && K / 128 % ksplit) return 0;   // gemm_kernel splits between other values of k, which would be other sums
   const int k = K / ksplit;
   const bool cand = kind == 3;
   if (cand && (M <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
@@ -146,13 +148,15 @@ inline int gemm_lds_variant(int M, int N, int K, int kind, int ksplit, bool ragg
   if (!cand && M <= 256 && k <= 512 && (M < 128 || (long)((M + 127) / 128) * ((N + 127) / 128) < 200)) return 0;
   long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   if (!cand && k >= 1024 && tiles64 <= 128) return 0;
-  // Up to here the padded rows decide, ragged or not: gemm_kernel may add its sums up in another order, and a batch without
-  // its padding has the bits of the padded one.  All tiles below add in the order of k.
+  // The sums have the bits of gemm_kernel's, so those of a ragged batch are the padded one's: the padded rows say how many
+  // groups of k there are (64 x 64 tiles only).
+  const int groups = cand ? 1 : gemm_k_groups(M, N, K, ksplit, kind == 2);
   if (ragged) M = M - M * 3 / 10;
   tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   int best = 0;
   float best_us = 0.f;
   for (int v = 1; v <= kLdsVariants; ++v) {
+    if (groups > 1 && v > 2) break;
     if (cand ? v < 3 || v > 5 : (v == 1 && (k % 128 || k > 512)) || (v == 2 && k > 512 && tiles64 > 256)) continue;
     const LdsModel& m = cand ? kLdsCandModels[v - 3] : kLdsModels[v - 1];
     const float tiles = (float)((M + m.bm - 1) / m.bm) * (float)((N + m.bn - 1) / m.bn) * (float)ksplit / 256.f;
@@ -188,6 +192,14 @@ inline int gemm_pick_tile(int M, int N, int K, int dtype, bool can_split) {
 inline int gemm_tile_shape(int M, int N, int ksplit, int chunks) {
   const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64) * ksplit;
   return tiles64 <= 64 && chunks >= 8 ? 2 : tiles64 <= 192 && chunks >= 4 ? 1 : 0;
+}
+
+// Groups of waves to which gemm_kernel deals the chunks of a bf16 product's k (launch_gemm): the sums of the groups are added
+// up in order, in gemm_lds.hip as well.
+inline int gemm_k_groups(int M, int N, int K, int ksplit, bool partials) {
+  if (gemm_pick_tile(M, N, K, 1, partials) == 3) return 1;
+  const int shape = gemm_tile_shape(M, N, ksplit, (K / 64 + ksplit - 1) / ksplit);
+  return shape == 2 ? 4 : shape == 1 ? 2 : 1;
 }
 
 // Small fp32 products through bf16 parts with k dealt to the waves (gemm_kwaves.hip): which tile, or 0 for gemm_kernel.

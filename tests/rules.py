@@ -15,6 +15,7 @@ extern "C" int skinny(int dtype, int M, int N, int K, int kind, int ks) { return
 extern "C" int small_model(int d, int F, int V, int layers, int beam, int batch) { return san::small_model_faster(d, F, V, layers, beam, batch); }
 extern "C" int small_model_at(int d, int F, int V, int layers, int beam, int batch, int H, int keys) { return san::small_model_faster(d, F, V, layers, beam, batch, H, (float)keys); }
 extern "C" int lds_variant(int M, int N, int K, int kind, int ks, int ragged) { return san::gemm_lds_variant(M, N, K, kind, ks, ragged != 0); }
+extern "C" int k_groups(int M, int N, int K, int ks, int partials) { return san::gemm_k_groups(M, N, K, ks, partials != 0); }
 extern "C" int kwaves_variant(int M, int N, int K, int ks) { return san::gemm_kwaves_variant(M, N, K, ks); }
 extern "C" int cand_n(int N) { return san::gemm_skinny_cand_n(N); }
 extern "C" int pick_ksplit(int M, int N, int K, int dtype) { return san::gemm_pick_ksplit(M, N, K, dtype, false); }

@@ -531,6 +531,21 @@ def test_bf16_products_straight_to_lds_match_oracle(case):
     gpu.close()
 
 
+# The 64 x 64 tiles add up as gemm_kernel's groups of waves do: a row's logits in a batch of 300 (straight to LDS) and in a
+# smaller one (gemm_kernel) of as many groups are the same bits.  Groups of 128 values of k, and of 64.
+@pytest.mark.parametrize("d,V,few,variant,groups", [(512, 764, 16, 1, 4), (512, 2004, 256, 1, 2), (448, 1004, 256, 2, 2), (576, 764, 16, 2, 4),
+                                                    (768, 764, 16, 2, 4), (1024, 2004, 256, 2, 2), (1088, 2004, 256, 2, 2)])
+def test_bf16_products_straight_to_lds_add_up_like_gemm_kernel(d, V, few, variant, groups):
+    L = rules.lib()
+    assert L.lds_variant(300, V, d, 1, 1, 0) == variant and L.lds_variant(few, V, d, 1, 1, 0) == 0 and L.skinny(1, few, V, d, 1, 1) == 0
+    assert L.k_groups(300, V, d, 1, 0) == L.k_groups(few, V, d, 1, 0) == groups
+    rng = np.random.default_rng(5)
+    row, w_out = (wl.round_to_bf16(x.astype(np.float32)) for x in (rng.normal(size=d), rng.normal(size=(V, d))))
+    got = [_logits_of(_cfg(dtype="bf16", batch=n, d=d, H=d // 64, F=64, V=V, n_dec=1, self_pi=[1], encdec_pi=[1], src_len=(1, 2)), row, w_out, 0)
+           for n in (few, 300)]
+    assert np.array_equal(got[1], np.broadcast_to(got[0][0], got[1].shape)) and np.array_equal(got[0], got[1][:few])
+
+
 # The logits may lie on any 4-byte boundary.
 @pytest.mark.parametrize("rows", [40, 300])
 def test_bf16_logits_on_a_4_byte_boundary(rows):
