@@ -205,7 +205,7 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // 16 bytes per lane from base + off (bytes) straight to LDS at lds + 16 * lane (lds: byte offset, uniform).  Counted by
 // vmcnt like any load; the compiler does not know of it, so the waits stand in the kernel.
 __device__ __forceinline__ void load_to_lds(const void* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(off), "s"(base) : "memory");
 }
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
