@@ -144,7 +144,7 @@ __global__ __launch_bounds__(WM* WN * 64) void lds_kernel(GemmParams p) {
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // a fragment read
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
+    if constexpr (TM * TN > TM + TN) __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
   auto piece = [&](int c, int s) { return (c % ST) * STAGE + ((s * 2 + kh) ^ sw) * 16; };
