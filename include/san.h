@@ -79,8 +79,9 @@ typedef struct {
                                      off in san_topk                                          */
   int32_t debug;       /* sum of: 1 keep per-layer S / A / hidden copies for san_debug_get;
                           2 run only the general-purpose attention kernel (no matrix-core
-                          kernel for the encoder memory) and fp32 products by the fp32
-                          instructions only: a cross-check, slower                         */
+                          kernel for the encoder memory), fp32 products by the fp32
+                          instructions only and small models by a launch per operation:
+                          a cross-check, slower                                            */
   float ln_eps;        /* LayerNorm epsilon                                           */
 } san_config;
 
@@ -141,6 +142,11 @@ SAN_API int san_rewind(san_ctx* ctx);
  * batch*beam rows: embeds tokens at the current position, runs every decoder
  * layer under the sharing policy, appends this position's keys/values to the
  * cache and writes the output-layer logits.
+ * Small fp32 models (cached dot-product self-attention, d_model 64 or 128, d_ff
+ * 64, 128, 256 or 512, beam <= 8, and weights, batch and positions for which that is
+ * the faster way) run a step in one launch, a workgroup per sentence; a decode may go
+ * from there to a launch per operation as its positions grow.  The results differ by
+ * the roundings of fp32 sums.
  *   tokens_dev DEVICE int32 [batch*beam] (ids outside [0,vocab) are clamped),
  *   logits_dev DEVICE fp32 [batch*beam][vocab].
  * Errors: SAN_ESTATE (no san_encode yet), SAN_ECAPACITY (step == max_tgt_len). */
@@ -220,7 +226,9 @@ SAN_API int san_debug_get(san_ctx* ctx, int32_t what, int32_t layer, void* dst_d
  * flags (SAN_LOOP_*, or-ed):
  *   SAN_LOOP_GRAPH: pairs of steps are replayed from a captured HIP graph (needs a
  *     stream other than the NULL stream and use_cache = 1; the graph is
- *     re-captured when the output/scratch pointers or the batch change).
+ *     re-captured when the output/scratch pointers or the batch change).  Where a small
+ *     model's steps run in one launch (see san_decode_step), all n of them do, or with
+ *     eos_id >= 0 the 8 between two checks, and nothing is captured.
  *   SAN_LOOP_COMPACT (needs use_cache = 1; no effect with eos_id < 0): at those
  *     8-step checks, once at least a quarter of the batch is finished and 16 or
  *     more steps remain, the finished sentences leave the batch (san_compact) and
@@ -335,12 +343,16 @@ enum {
  * loops).  san_profile_read adds up, per class, the elapsed milliseconds and
  * the number of launches since the last reset.  The markers themselves cost
  * about 2 us per bracketed launch, included in the figures.
+ * Steps of small models run by a launch per operation while profiling is on, so the
+ * figures are not of the one launch that runs otherwise.
  *   ms_out HOST double[SAN_K_COUNT], launches_out HOST int64[SAN_K_COUNT]
  *   (either may be NULL). */
 SAN_API int san_profile(san_ctx* ctx, int32_t enable);
 SAN_API int san_profile_read(san_ctx* ctx, double* ms_out, int64_t* launches_out, int32_t reset);
 
-/* Number of kernels the last san_decode_step queued. */
+/* Number of kernels that the decoder queued for the last step, its beam step not
+ * counted: of san_decode_step, or the last one of san_decode_n (1 where one launch ran
+ * several steps, their beam steps included). */
 SAN_API int32_t san_last_launch_count(const san_ctx* ctx);
 
 /* Message of the last failed call on this context ("" if none).  With ctx ==

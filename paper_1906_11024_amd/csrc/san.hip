@@ -1626,6 +1626,7 @@ int san_decode_n(san_ctx* c, int32_t n, const int32_t* tokens_dev, float* cum_io
       p.out_tok = out_tokens_dev; p.out_par = out_parents_dev;
       p.step0 = done; p.out_ld = rows0; p.row_map = compacted ? c->row_map : nullptr;
       p.feed_last = fused;
+      c->launches = 0;
       LAUNCH(c, launch_small_decode(p, c->batch, c->stream));
       c->t += p.steps;
       done += p.steps;

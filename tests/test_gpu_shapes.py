@@ -448,6 +448,25 @@ def test_small_models_loop_equals_the_launches(eos, compact, beam):
         assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
 
 
+def test_small_models_count_the_launches_of_the_last_step():
+    cfg = _cfg(batch=2, steps=12)
+    w = wl.make_weights(cfg, seed=5)
+    src, lens = wl.make_source(cfg, 5)
+    gpu = hz.make_gpu(cfg, w)
+    gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+    tok, toks, pars = torch.full((2,), wl.BOS_ID, dtype=torch.int32, device="cuda"), *torch.zeros(2, 4, 2, dtype=torch.int32, device="cuda")
+    logits = torch.empty(2, cfg["V"], device="cuda")
+    for _ in range(2):
+        gpu.decode_n(4, tok, torch.zeros(2, device="cuda"), toks, pars, logits)
+        assert gpu.last_launch_count == 1
+    gpu.decode_step(tok, logits)
+    assert gpu.last_launch_count == 1
+    gpu.profile(True)                                        # the general route
+    gpu.decode_step(tok, logits)
+    assert gpu.last_launch_count > 10
+    gpu.close()
+
+
 # The rule counts the positions that are read: a decode goes from one launch a step to the launches of the general route.
 @pytest.mark.parametrize("loop", [None, "cands"])
 @pytest.mark.parametrize("beam,H,src", [(8, 4, 420), (4, 1, 612)])
