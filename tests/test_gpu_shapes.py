@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 from paper_1906_11024_amd import workloads as wl
 from tests import harness as hz
 from tests import rules
-from tests.test_gpu_parity import BF16_TOL, F32_TOL
+from tests.test_gpu_parity import BF16_TOL, F32_TOL, _compaction_schedule
 
 
 def _cfg(**kw):
@@ -407,11 +407,12 @@ def test_small_models_match_oracle(case, loop):
     ls.gpu.close()
 
 
-# Several steps inside one launch, with and without end symbols, graph flag and compaction, then single steps on the state
-# they leave, against the launches (debug = 2) on the same weights.  The seed's searches have no near ties: scores differ by
-# the roundings of 32-bit sums (2e-5 of sums of up to 40 log-probabilities).
-@pytest.mark.parametrize("eos,compact,beam", [(-1, False, 4), (wl.EOS_ID, False, 4), (wl.EOS_ID, True, 4), (-1, False, 1)])
-def test_small_models_loop_equals_the_launches(eos, compact, beam):
+# Several steps inside one launch, with and without end symbols and the graph flag, then single steps on the state they leave,
+# against the launches (debug = 2) on the same weights.  The seed's searches have no near ties: scores differ by
+# the roundings of 32-bit sums (2e-5 of sums of up to 40 log-probabilities).  (21 steps: no sentence leaves the batch; see
+# test_small_models_drop_finished_sentences.)
+@pytest.mark.parametrize("eos,compact,beam,graph", [(-1, False, 4, True), (wl.EOS_ID, False, 4, False), (wl.EOS_ID, True, 4, True), (-1, False, 1, False)])
+def test_small_models_loop_equals_the_launches(eos, compact, beam, graph):
     cfg = _cfg(batch=6, beam=beam, steps=44, V=260, src_len=(2, 9))
     assert rules.lib().small_model(cfg["d"], cfg["F"], cfg["V"], cfg["n_dec"], beam, cfg["batch"])
     w = wl.make_weights(cfg, seed=5, sharp=4.0)
@@ -420,32 +421,112 @@ def test_small_models_loop_equals_the_launches(eos, compact, beam):
         w["w_out"][eos] *= np.float32(2.0)     # some sentences end early
     src, lens = wl.make_source(cfg, 5)
     rows, out = cfg["batch"] * beam, []
-    for debug in (0, 2):
-        gpu = hz.make_gpu(cfg, w, eos_id=eos, debug=debug)
-        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
-        tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
-        cum = torch.full((cfg["batch"], beam), -float("inf"), device="cuda")
-        cum[:, 0] = 0.0
-        cum = cum.reshape(-1).contiguous()
-        toks = torch.zeros(40, rows, dtype=torch.int32, device="cuda")
-        pars = torch.zeros_like(toks)
-        logits = torch.empty(rows, cfg["V"], device="cuda")
-        gpu.decode_n(21, tok, cum, toks, pars, logits, compact=compact)
-        step, active = gpu.step, gpu.active()
-        more = []
-        if len(active) == cfg["batch"] and step == 21:
-            t2, c2 = toks[20].clone(), cum.clone()
-            gpu.decode_n(3, t2, c2, toks[21:], pars[21:], logits)
-            gpu.decode_step(toks[23].clone(), logits)
-            more = [c2.cpu().numpy(), logits.cpu().numpy()]
-        out.append((step, list(active), toks.cpu().numpy(), pars.cpu().numpy(), cum.cpu().numpy(), *more))
-        gpu.close()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for debug in (0, 2):
+            gpu = hz.make_gpu(cfg, w, eos_id=eos, debug=debug)
+            gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+            tok = torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda")
+            cum = torch.full((cfg["batch"], beam), -float("inf"), device="cuda")
+            cum[:, 0] = 0.0
+            cum = cum.reshape(-1).contiguous()
+            toks = torch.zeros(40, rows, dtype=torch.int32, device="cuda")
+            pars = torch.zeros_like(toks)
+            logits = torch.empty(rows, cfg["V"], device="cuda")
+            gpu.decode_n(21, tok, cum, toks, pars, logits, use_graph=graph, compact=compact)
+            step, active = gpu.step, gpu.active()
+            more = []
+            if len(active) == cfg["batch"] and step == 21:
+                t2, c2 = toks[20].clone(), cum.clone()
+                gpu.decode_n(3, t2, c2, toks[21:], pars[21:], logits)
+                gpu.decode_step(toks[23].clone(), logits)
+                more = [c2.cpu().numpy(), logits.cpu().numpy()]
+            out.append((step, list(active), toks.cpu().numpy(), pars.cpu().numpy(), cum.cpu().numpy(), *more))
+            gpu.close()
     a, b = out
     assert a[0] == b[0] and a[1] == b[1] and len(a) == len(b)
     assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
     for x, y in zip(a[4:], b[4:]):
         fin = np.isfinite(y)
         assert np.array_equal(np.isfinite(x), fin) and np.abs(x[fin] - y[fin]).max() <= 2e-5 * np.abs(y[fin]).max()
+
+
+# Sentences that leave the batch between two launches of several steps (row map, sentence index, caches wider than the batch,
+# the loop's words and scores moved up), once and twice (seed 23), down to one sentence, against the oracle's search on the
+# full batch.
+@pytest.mark.parametrize("beam,eos_scale,seed,left", [(4, 1.6, 10, 6), (2, 2.5, 34, 1), (2, 2.5, 23, 2), (1, 2.0, 2, 3), (3, 2.0, 3, 2)])
+def test_small_models_drop_finished_sentences(beam, eos_scale, seed, left):
+    batch, T = 8, 40
+    cfg = _cfg(batch=batch, beam=beam, V=132, steps=T, src_len=(2, 9))
+    rows = batch * beam
+    assert rules.lib().small_model(cfg["d"], cfg["F"], cfg["V"], cfg["n_dec"], beam, batch)
+    w = wl.make_weights(cfg, seed=seed, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(8.0)
+    w["w_out"][wl.EOS_ID] *= np.float32(eos_scale)
+    src, lens = wl.make_source(cfg, seed)
+    ref = hz.make_oracle(cfg, w, eos_id=wl.EOS_ID).search(src, lens, T, beam)
+    assert ref["margin"] > 2e-4 and hz.smallest_score_gap(ref, batch, beam) > 1e-4   # no near ties
+    done = np.stack([(ref["tokens"][t].reshape(batch, beam) == wl.EOS_ID).all(axis=1) for t in range(T)])
+    steps, active = _compaction_schedule(done, T)
+    assert len(active) == left < batch
+    with torch.cuda.stream(torch.cuda.Stream()):
+        gpu = hz.make_gpu(cfg, w, eos_id=wl.EOS_ID, steps=T + 4)
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty((rows, cfg["V"]), device="cuda")
+        for graph in (False, True):
+            gpu.rewind()
+            assert gpu.batch == batch
+            toks, pars = (torch.full((T, rows), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+            cum = torch.full((batch, beam), -np.inf, device="cuda")
+            cum[:, 0] = 0.0
+            cum = cum.reshape(-1).contiguous()
+            gpu.decode_n(T, torch.full((rows,), wl.BOS_ID, dtype=torch.int32, device="cuda"), cum, toks, pars, logits, use_graph=graph, compact=True)
+            assert gpu.last_launch_count == 1 and gpu.step == steps and gpu.active().tolist() == active.tolist()
+            got = [x.cpu().numpy() for x in (toks, pars, cum)]
+            for t in range(steps):
+                assert np.array_equal(got[0][t], ref["tokens"][t].reshape(-1)) and np.array_equal(got[1][t], ref["parents"][t].reshape(-1)), t
+            assert (got[0][steps:] == -7).all() and (got[1][steps:] == -7).all()
+            np.testing.assert_allclose(got[2], ref["scores"][steps - 1].reshape(-1), rtol=0, atol=1e-3)
+        gpu.close()
+
+
+# The same by san_compact between single steps and between calls of the loop.
+@pytest.mark.parametrize("share,loop", [("A", None), ("S", None), ("A", "cands"), ("S", "cands")])
+def test_small_models_go_on_after_compaction(share, loop):
+    cfg = _cfg(batch=7, beam=3, V=260, steps=16, src_len=(0, 9), encdec_pi=[3])
+    assert rules.lib().small_model(cfg["d"], cfg["F"], cfg["V"], cfg["n_dec"], 3, 7)
+    w = wl.make_weights(cfg, seed=9, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(8.0)
+    src, lens = wl.make_source(cfg, 9)
+    gpu = hz.make_gpu(cfg, w, share=share, max_batch=9)
+    ls = hz.Lockstep(gpu, hz.make_oracle(cfg, w, share=share), src, lens, 3, subset=[2, 5], loop=loop)
+    for t in range(14):
+        if t == 5:
+            hz.lockstep_compact(ls, [0, 2, 3, 5, 6])
+        if t == 9:
+            hz.lockstep_compact(ls, [1, 3])
+            assert gpu.active().tolist() == [2, 5]
+        ls.step(logit_tol=F32_TOL)
+        assert gpu.last_launch_count == 1
+    assert loop or max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
+    gpu.close()
+
+
+# Scores of all words and rows do not fit the LDS of a workgroup beside a long history: single steps run in one launch, the
+# loop's search by the launches, on one state.
+def test_small_models_whose_search_does_not_fit_the_lds():
+    cfg = _cfg(batch=2, beam=8, F=64, V=4000, steps=12)
+    assert rules.lib().small_model(64, 64, 4000, 3, 8, 2)
+    w = wl.make_weights(cfg, seed=31, sharp=4.0)
+    w["w_out"] = w["w_out"] * np.float32(8.0)
+    src, lens = wl.make_source(cfg, 31)
+    gpu = hz.make_gpu(cfg, w, steps=600)
+    ls = hz.Lockstep(gpu, hz.make_oracle(cfg, w, max_len=600), src, lens, 8)
+    for t in range(12):
+        ls.loop = "cands" if t % 3 == 2 else None
+        ls.step(logit_tol=F32_TOL)
+        assert (gpu.last_launch_count == 1) == (ls.loop is None)
+    assert max(ls.log["logit_err"]) <= F32_TOL, max(ls.log["logit_err"])
+    gpu.close()
 
 
 def test_small_models_count_the_launches_of_the_last_step():
