@@ -729,12 +729,14 @@ def test_decode_n_candidate_output_layer_matches_oracle(case):
     gpu.close()
 
 
-@pytest.mark.parametrize("shape", ["64x64", "64x64_4_live", "128x128"])
+@pytest.mark.parametrize("shape", ["small_model", "small_model_4_live", "64x64", "64x64_4_live", "128x128"])
 def test_decode_n_all_equal_logits_take_the_lowest_ids(shape):
     """A zero output embedding makes every logit 0: every candidate of a sentence ties and the
     order (higher score, then lower beam * vocab + word) alone decides, in every column tile's
-    exhaustive path (more entries at the threshold than slots) and in the combine."""
-    over = {"64x64": dict(batch=5, V=2004), "64x64_4_live": dict(batch=5, V=1988), "128x128": dict()}[shape]
+    exhaustive path (more entries at the threshold than slots) and in the combine; or in the waves' rounds and the merge of
+    the decoder with one workgroup per sentence (small_model)."""
+    over = {"small_model": dict(batch=5, V=2004), "small_model_4_live": dict(batch=5, V=1988), "64x64": dict(batch=5, V=2004, F=192),
+            "64x64_4_live": dict(batch=5, V=1988, F=192), "128x128": dict()}[shape]
     cfg = dict(WIDE)
     cfg.update(over)
     beam, B, steps = cfg["beam"], cfg["batch"] * cfg["beam"], 4
@@ -754,6 +756,7 @@ def test_decode_n_all_equal_logits_take_the_lowest_ids(shape):
     for t in range(steps):
         assert np.array_equal(out_tok[t].cpu().numpy(), ref["tokens"][t]), (shape, t)
         assert np.array_equal(out_par[t].cpu().numpy(), ref["parents"][t]), (shape, t)
+    assert (gpu.last_launch_count == 1) == shape.startswith("small_model")
     assert np.array_equal(ref["tokens"][0].reshape(-1, beam), np.tile(np.arange(beam), (cfg["batch"], 1)))
     np.testing.assert_allclose(cum.cpu().numpy(), ref["scores"][steps - 1], rtol=0, atol=1e-4)
     gpu.close()
@@ -1055,11 +1058,11 @@ def test_decode_n_drops_finished_sentences(seed, use_graph):
 
 
 # ------------------------------------------------------ head widths, extreme shapes
-@pytest.mark.parametrize("d,H,dtype", [(128, 8, "f32"), (128, 4, "f32"), (256, 2, "f32"), (128, 8, "bf16"),
-                                       (256, 8, "bf16"), (256, 2, "bf16")])
+@pytest.mark.parametrize("d,H,dtype", [(128, 8, "f32"), (128, 4, "f32"), (192, 12, "f32"), (192, 6, "f32"), (256, 2, "f32"),
+                                       (128, 8, "bf16"), (256, 8, "bf16"), (256, 2, "bf16")])
 def test_head_widths(d, H, dtype):
     """Head widths 16, 32 and 128 take other lane mappings of the attention kernel
-    than the 64 of the paper's models."""
+    than the 64 of the paper's models (fp32 models of 128 columns: of the decoder with one workgroup per sentence)."""
     cfg = mid_cfg(d=d, H=H, F=2 * d, dtype=dtype, steps=37, batch=3, beam=3, self_pi=[2, 2], encdec_pi=[1, 3])
     w = wl.make_weights(cfg, seed=17, sharp=3.0)
     src, lens = ragged(cfg, 17)
@@ -1069,6 +1072,7 @@ def test_head_widths(d, H, dtype):
         for t in range(cfg["steps"]):
             ls.step(logit_tol=F32_TOL if dtype == "f32" else BF16_TOL)
         assert max(ls.log["logit_err"]) <= (F32_TOL if dtype == "f32" else BF16_TOL), (share, max(ls.log["logit_err"]))
+        assert (gpu.last_launch_count == 1) == (d == 128 and dtype == "f32")
         gpu.close()
 
 

@@ -39,8 +39,10 @@ def _lockstep(cfg, share="A", loop=None, seed=31, **kw):
 
 
 _FEW = {
-    # one row; fewer 64-byte units of k (4, bf16: 2) than the eight waves that share them; ragged vocabulary
+    # one row; fewer 64-byte units of k (4, bf16: 2) than the eight waves that share them; ragged vocabulary.  (F = 128: one
+    # launch a step.)
     "one_row": dict(),
+    "one_row_f192": dict(F=192),
     "one_row_bf16": dict(dtype="bf16", F=64),
     # the last row count of the products of few rows, and the first beyond it
     "rows16": dict(batch=4, beam=4, d=512, H=8, F=1024, V=16388),
@@ -65,6 +67,7 @@ def test_few_rows_match_oracle(case, loop):
     cfg = _cfg(**_FEW[case])
     share = cfg.pop("share", "A")
     ls = _lockstep(cfg, share, loop)
+    assert (ls.gpu.last_launch_count == 1) == (case == "one_row")
     if loop is None:
         assert max(ls.log["logit_err"]) <= _tol(cfg), max(ls.log["logit_err"])
     ls.gpu.close()
@@ -102,9 +105,19 @@ def test_few_rows_on_both_sides_of_the_rule(dtype, d, batch, beam, few, kw, loop
     ("bf16", 256, 520, 4, (2, 1)), ("bf16", 512, 17, 2, (4, 4)), ("f32", 576, 17, 2, (8, 8)), ("f32", 768, 17, 6, (8, 4)),
     ("bf16", 640, 17, 2, (4, 4)), ("bf16", 768, 72, 6, (4, 2)), ("f32", 1024, 72, 4, (8, 2)), ("f32", 1024, 17, 4, (16, 4))])
 def test_layer_norms_over_split_products(dtype, d, rows, block, splits):
+    _layer_norms(dtype, d, rows, block, splits, 64)
+
+
+# F = 192: no one-workgroup decoder, the LayerNorms are launches.
+@pytest.mark.parametrize("d,splits", [(64, (1, 1)), (128, (2, 2))])
+def test_layer_norms_over_split_products_of_narrow_models(d, splits):
+    assert _layer_norms("f32", d, 17, 2, splits, 192) > 10
+
+
+def _layer_norms(dtype, d, rows, block, splits, F):
     dt = 1 if dtype == "bf16" else 0
     assert (rules.lib().pick_ksplit(rows, d, d, dt), rules.lib().pick_ksplit(rows, block * d, d, dt)) == splits
-    cfg = _cfg(dtype=dtype, d=d, H=d // 64, F=64, V=260, batch=rows, n_dec=block, self_pi=[block], encdec_pi=[block], steps=2)
+    cfg = _cfg(dtype=dtype, d=d, H=d // 64, F=F, V=260, batch=rows, n_dec=block, self_pi=[block], encdec_pi=[block], steps=2)
     w = wl.make_weights(cfg, seed=8, sharp=4.0)
     src, lens = wl.make_source(cfg, 8)
     gpu = hz.make_gpu(cfg, w)
@@ -112,7 +125,9 @@ def test_layer_norms_over_split_products(dtype, d, rows, block, splits):
     for _ in range(cfg["steps"]):
         ls.step(logit_tol=_tol(cfg))
     assert max(ls.log["logit_err"]) <= _tol(cfg), max(ls.log["logit_err"])
+    launches = gpu.last_launch_count
     gpu.close()
+    return launches
 
 
 # a wide vocabulary whose last column tile has 4 live columns, k = 192 (an odd number of chunk pairs) and 256; wm: tiles
