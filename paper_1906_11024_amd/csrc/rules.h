@@ -265,9 +265,11 @@ inline int gemm_pick_ksplit(int M, int N, int K, int dtype, bool plain) {
   const long blocks = (long)((M + 63) / 64) * ((N + 63) / 64);
   // aim for >= 256 blocks (one per CU), keep at least 2 chunks of k per block
   while (blocks * ks < 256 && nchunks / (ks * 2) >= 2 && ks < 16) ks *= 2;
-  // A long k (the feed-forward's second product): gemm_kwaves.hip needs fewer splits, and its consumer adds fewer partials
-  // (LayerNorm of 185 rows over 16 4.9 us, over 4 4.5).  us, the split above / the one taken: 185 x 512 x 2048 8.3 (16) /
-  // 7.4 (2), 128 rows 5.9 (16) / 5.6 (4), 256 rows 8.5 (8) / 8.4 (2).  Products that are as wide as long gain nothing.
+  // A long k (the feed-forward's second product): gemm_kwaves.hip needs fewer splits, and its consumer adds fewer partials.
+  // us, alone and with the LayerNorm behind it, the split above / the one taken: 128 x 512 x 2048 (16) 5.8 and 10.0 / (4) 5.6 and
+  // 8.7, 185 rows (16) 8.4 and 13.8 / (4) 7.5 and 10.5, 256 rows (8) 8.2 and 12.3 / (4) 8.5 and 12.0, 300 rows (8) 11.1 and 15.3 /
+  // (2) 10.1 and 12.9.  (Two splits take 10.2 for 185 rows and their LayerNorm and 11.4 for 256, 9.8 for 128: a partial costs
+  // the LayerNorm more than is counted here.)  Products that are as wide as long gain nothing.
   float best_us = 0.f;
   if (dtype == 0 && !plain && M > 16 && K >= 2 * N) {
     gemm_kwaves_variant(M, N, K, ks, &best_us);

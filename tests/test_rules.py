@@ -42,6 +42,13 @@ def test_bf16_products_get_a_tile_that_can_take_them():
     assert {v for _, v in seen} == set(range(1, 8)) and {v for kd, v in seen if kd == 3} == {3, 4, 5}
 
 
+def test_splits_of_products_over_a_long_k():
+    L = rules.lib()
+    for m, n, k, ks in ((40, 512, 2048, 8), (64, 512, 2048, 8), (100, 512, 2048, 4), (128, 512, 2048, 4), (185, 512, 2048, 4), (256, 512, 2048, 4),
+                        (300, 512, 2048, 2), (128, 1024, 4096, 4), (185, 1024, 4096, 2), (185, 512, 1024, 2), (256, 256, 1024, 4)):
+        assert L.pick_ksplit(m, n, k, 0) == ks and L.kwaves_variant(m, n, k, ks) and not L.split_wm(m, n, k, ks, ks), (m, n, k)
+
+
 def test_padding_does_not_choose_the_kernel_of_a_bf16_product():
     """A ragged batch has the bits of the padded one: gemm_kernel, which may add up in another order, takes both or neither."""
     L = rules.lib()
