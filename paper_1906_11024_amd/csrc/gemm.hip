@@ -2,7 +2,7 @@
 //
 // out[m][n] = sum_k A[m][k] * W[n][k]: both operands are contiguous along k, so a
 // lane's MFMA operand fragment is one 16-byte load.  A block of WM x WN waves
-// owns a (32*WM*TM) x (32*WN*TN) tile of the output; k is walked in chunks of 128
+// owns a (32*WM) x (32*WN) tile of the output; k is walked in chunks of 128
 // (bf16: 256) bytes per row.  Decode-time GEMMs are small (M = batch*beam rows) and therefore
 // latency-bound, so the kernel is built to keep many loads in flight: a queue of
 // D chunks lives in registers (global loads issued D chunks ahead), each chunk is
@@ -54,18 +54,18 @@ template <> __device__ __forceinline__ void mma_frag<bf16_t>(f32x16& acc, const 
 // reduce each row of BN columns to (max, sum of exp(x - max)) and a few entries that
 // include its p.cand_k largest (see GemmParams::cand_*): the beam step needs nothing
 // else of the output layer.
-template <typename T, int WM, int WN, int TM, int TN, int KW, int D, int CB, bool CAND>
+template <typename T, int WM, int WN, int KW, int D, int CB, bool CAND>
 __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
   constexpr int kRowBytes = CB + 16;
   constexpr int SEGS = CB / 16;                      // 16-byte segments of a row chunk
   constexpr int NG = WM * WN * 64;                   // threads of one k-group
-  constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
+  constexpr int BM = 32 * WM, BN = 32 * WN;
   constexpr int EPC = CB / (int)sizeof(T);           // elements per chunk
   constexpr int RPP = NG / SEGS;                     // rows covered by one pass of 16-byte loads
   constexpr int LA = BM / RPP, LB = BN / RPP;        // 16-byte loads per thread per chunk
   constexpr int STAGE = 2 * (BM + BN) * kRowBytes;   // LDS bytes of one k-group (double buffered)
   static_assert(BM % RPP == 0 && BN % RPP == 0 && D % 2 == 0, "tile shape");
-  static_assert(KW == 1 || (KW - 1) * (WM * WN) * TM * TN * 16 * 64 * 4 <= KW * STAGE, "reduction fits the stages");
+  static_assert(KW == 1 || (KW - 1) * (WM * WN) * 16 * 64 * 4 <= KW * STAGE, "reduction fits the stages");
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -98,12 +98,8 @@ __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
   // before every conditional store -- the counter it waits on also counts the
   // stores -- which serialises the 16 stores of a tile (+1.3 us on a 10 us GEMM).
   const int t_step = p.t_dev ? *p.t_dev : 0;
-  float bias_v[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + (wn * TN + j) * 32 + l32;
-    bias_v[j] = (p.bias && p.out_kind != 2 && kg == 0 && n < p.N) ? to_f32(reinterpret_cast<const T*>(p.bias)[n]) : 0.f;
-  }
+  const int n_own = n0 + wn * 32 + l32;   // this lane's column
+  float bias_v = (p.bias && p.out_kind != 2 && kg == 0 && n_own < p.N) ? to_f32(reinterpret_cast<const T*>(p.bias)[n_own]) : 0.f;
   const int nchunks = p.K / EPC;
   const int cps = p.cps;   // chunks per k-split, (nchunks + ksplit - 1) / ksplit, divided on the host
   const int c_begin = blockIdx.z * cps;
@@ -144,20 +140,16 @@ __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
         *reinterpret_cast<u32x4*>(Ws + ((buf_) * BN + lrow + RPP * i_) * kRowBytes + lseg * 16) = qw[s_][i_]; \
   } while (0)
 
-  f32x16 acc[TM][TN];
+  f32x16 acc;
 
 #define SAN_MMA(buf_)                                                                                      \
   do {                                                                                                     \
-    const unsigned char* xs_ = Xs + ((buf_) * BM + wm * 32 * TM + l32) * kRowBytes + kh * 16;              \
-    const unsigned char* ws_ = Ws + ((buf_) * BN + wn * 32 * TN + l32) * kRowBytes + kh * 16;              \
+    const unsigned char* xs_ = Xs + ((buf_) * BM + wm * 32 + l32) * kRowBytes + kh * 16;                   \
+    const unsigned char* ws_ = Ws + ((buf_) * BN + wn * 32 + l32) * kRowBytes + kh * 16;                   \
     _Pragma("unroll") for (int sub_ = 0; sub_ < CB / 32; ++sub_) {                                         \
-      u32x4 xf_[TM], wf_[TN];                                                                              \
-      _Pragma("unroll") for (int i_ = 0; i_ < TM; ++i_)                                                    \
-          xf_[i_] = *reinterpret_cast<const u32x4*>(xs_ + i_ * 32 * kRowBytes + sub_ * 32);                \
-      _Pragma("unroll") for (int j_ = 0; j_ < TN; ++j_)                                                    \
-          wf_[j_] = *reinterpret_cast<const u32x4*>(ws_ + j_ * 32 * kRowBytes + sub_ * 32);                \
-      _Pragma("unroll") for (int i_ = 0; i_ < TM; ++i_)                                                    \
-          _Pragma("unroll") for (int j_ = 0; j_ < TN; ++j_) mma_frag<T>(acc[i_][j_], xf_[i_], wf_[j_]);    \
+      const u32x4 xf_ = *reinterpret_cast<const u32x4*>(xs_ + sub_ * 32);                                  \
+      const u32x4 wf_ = *reinterpret_cast<const u32x4*>(ws_ + sub_ * 32);                                  \
+      mma_frag<T>(acc, xf_, wf_);                                                                          \
     }                                                                                                      \
   } while (0)
 
@@ -168,19 +160,13 @@ __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
   // of the register queue from D chunks to one and made every chunk cost a full
   // memory latency.  Chunk indices past the end are clamped (the data is loaded
   // and never used) instead of skipped.
-#define SAN_INIT_ACC()                                                                   \
-  do {                                                                                   \
-    _Pragma("unroll") for (int i_ = 0; i_ < TM; ++i_)                                    \
-        _Pragma("unroll") for (int j_ = 0; j_ < TN; ++j_)                                \
-            _Pragma("unroll") for (int v_ = 0; v_ < 16; ++v_) acc[i_][j_][v_] = bias_v[j_]; \
-  } while (0)   /* column n of every row this lane holds */
+#define SAN_INIT_ACC()                                                   \
+  do {                                                                   \
+    _Pragma("unroll") for (int v_ = 0; v_ < 16; ++v_) acc[v_] = bias_v;  \
+  } while (0)   /* the column of every row this lane holds */
   if (iters <= 0) {   // an empty k-slice of a split GEMM (those carry no bias): contributes zeros
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   }
   if (iters > 0) {
     const int c_last = c_end - 1;
@@ -191,8 +177,7 @@ __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
     // the asm ties the start values to this point of the program (the loads
     // cannot sink below a memory clobber, the moves cannot rise above it), where
     // waiting for the bias means waiting for the oldest load only.
-#pragma unroll
-    for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(bias_v[j]) : : "memory");
+    asm volatile("" : "+v"(bias_v) : : "memory");
     SAN_INIT_ACC();
     // steady state: every chunk used here exists, every iteration refills its slot
     const int iters_main = iters > D ? ((iters - D) / D) * D : 0;
@@ -243,121 +228,79 @@ __global__ __launch_bounds__(WM* WN* KW * 64) void gemm_kernel(GemmParams p) {
   if (KW > 1) {
     // ---- add up the k-groups through LDS, in group order (deterministic)
     __syncthreads();   // all stages are dead now
-    float* red = reinterpret_cast<float*>(smem);   // [KW-1][waves per group][TM*TN*16][64]
+    float* red = reinterpret_cast<float*>(smem);   // [KW-1][waves per group][16][64]
     if (kg > 0) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            red[((((kg - 1) * (WM * WN) + w_in) * (TM * TN) + i * TN + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+      for (int v = 0; v < 16; ++v) red[(((kg - 1) * (WM * WN) + w_in) * 16 + v) * 64 + lane] = acc[v];
     }
     __syncthreads();
     if (kg > 0) return;
 #pragma unroll
     for (int g = 1; g < KW; ++g)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            acc[i][j][v] += red[((((g - 1) * (WM * WN) + w_in) * (TM * TN) + i * TN + j) * 16 + v) * 64 + lane];
+      for (int v = 0; v < 16; ++v) acc[v] += red[(((g - 1) * (WM * WN) + w_in) * 16 + v) * 64 + lane];
   }
 
   if constexpr (CAND) {
     static_assert(KW == 1, "the tile is complete in every wave");
     constexpr int LDW = BN + 4;                    // fp32 words per LDS row (16-byte multiple, rows 4 banks apart)
-    constexpr int PR = BM * LDW * 4 <= STAGE ? BM : (BM / 2 * LDW * 4 <= STAGE ? BM / 2 : BM / 4);   // rows per pass
     constexpr int NGRP = NG / 16;                  // 16-lane groups, one row each at a time
-    static_assert(PR % 32 == 0 && PR * LDW * 4 <= STAGE && PR % NGRP == 0, "candidate pass shape");
+    static_assert(BM * LDW * 4 <= STAGE && BM % NGRP == 0, "the tile fits the stages");
     float* tile = reinterpret_cast<float*>(smem);
-    const int l16 = lane & 15, grp = tid >> 4;
-    for (int pass = 0; pass < BM / PR; ++pass) {
-      __syncthreads();   // the k loop's stages (or the previous pass's rows) are dead
+    __syncthreads();   // the k loop's stages are dead
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int rb = (wm * TM + i) * 32 - pass * PR;
-        if (rb < 0 || rb >= PR) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int col = (wn * TN + j) * 32 + l32;
-          const bool live = n0 + col < p.N;
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            tile[(rb + (v >> 2) * 8 + kh * 4 + (v & 3)) * LDW + col] = live ? acc[i][j][v] : -INFINITY;
-        }
-      }
-      __syncthreads();
-      for (int r = grp; r < PR; r += NGRP) {
-        const int m = m0 + pass * PR + r;
-        emit_row_candidates<BN>(p, tile + r * LDW, m, m < p.M, tile_x, n0, l16);
-      }
-    }
+    for (int v = 0; v < 16; ++v)
+      tile[(wm * 32 + (v >> 2) * 8 + kh * 4 + (v & 3)) * LDW + wn * 32 + l32] = n_own < p.N ? acc[v] : -INFINITY;
+    __syncthreads();
+    for (int r = tid >> 4; r < BM; r += NGRP) emit_row_candidates<BN>(p, tile + r * LDW, m0 + r, m0 + r < p.M, tile_x, n0, lane & 15);
     if (p.bump && tile_x == 0 && tile_y == 0 && tid == 0) *p.bump = *p.bump + 1;
     return;
   }
 
-  // acc[i][j][v]: output row m = tile_m + (v/4)*8 + kh*4 + (v%4), column n = tile_n + l32.
+  // acc[v]: output row m = tile_m + (v/4)*8 + kh*4 + (v%4), column n = tile_n + l32.
   // For a fixed v the 32 lanes of a half-wave hold 32 consecutive columns of one
   // row, so every store instruction writes two contiguous 128-byte (fp32) row
   // segments -- whole cache lines, which matters for the wide output layer.
   // Row offsets: one 64-bit product per 32x32 tile (its first row); the other 15
   // rows are that plus a compile-time multiple of the row stride.
+  const int mrow = m0 + wm * 32 + kh * 4;
   if (p.out_kind == 2) {
     // ---- fp32 partials [ksplit][M][N]; the consumer (LayerNorm kernel) adds them up in a fixed order
-    float* part = reinterpret_cast<float*>(p.out[0]) + (size_t)blockIdx.z * p.M * p.N;
     const size_t ld = (size_t)p.N;
+    float* dst = reinterpret_cast<float*>(p.out[0]) + (size_t)blockIdx.z * p.M * p.N + (size_t)mrow * ld + n_own;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n0 + (wn * TN + j) * 32 + l32;
-        const int mrow = m0 + (wm * TM + i) * 32 + kh * 4;
-        float* dst = part + (size_t)mrow * ld + n;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int dm = (v >> 2) * 8 + (v & 3);
-          if (mrow + dm < p.M && n < p.N) dst[dm * ld] = acc[i][j][v];
-        }
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int dm = (v >> 2) * 8 + (v & 3);
+      if (mrow + dm < p.M && n_own < p.N) dst[dm * ld] = acc[v];
+    }
     return;
   }
 
   // ---- epilogue: ReLU, scatter into up to three column segments (the bias is already in)
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + (wn * TN + j) * 32 + l32;
-    if (n >= p.N) continue;
-    const int s = ((unsigned)n >= (unsigned)p.seg_w) + ((unsigned)n >= 2u * (unsigned)p.seg_w);   // n / seg_w, at most 2
-    const int nn = n - s * p.seg_w;
+  if (n_own < p.N) {
+    const int s = ((unsigned)n_own >= (unsigned)p.seg_w) + ((unsigned)n_own >= 2u * (unsigned)p.seg_w);   // n / seg_w, at most 2
+    const int nn = n_own - s * p.seg_w;
     void* obase = s == 0 ? p.out[0] : (s == 1 ? p.out[1] : p.out[2]);
     const size_t ld = (size_t)(s == 0 ? p.ldo[0] : (s == 1 ? p.ldo[1] : p.ldo[2]));
     const long long ts = s == 0 ? p.tstride[0] : (s == 1 ? p.tstride[1] : p.tstride[2]);
-    const size_t base = (size_t)t_step * ts + nn;
+    const size_t row0 = (size_t)t_step * ts + nn + (size_t)mrow * ld;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int mrow = m0 + (wm * TM + i) * 32 + kh * 4;
-      const size_t row0 = base + (size_t)mrow * ld;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int dm = (v >> 2) * 8 + (v & 3);
-        if (mrow + dm >= p.M) continue;
-        float val = acc[i][j][v];
-        if (p.flags & kGemmRelu) val = fmaxf(val, 0.f);
-        const size_t off = row0 + dm * ld;
-        if (p.out_kind == 1) reinterpret_cast<float*>(obase)[off] = val;
-        else reinterpret_cast<T*>(obase)[off] = from_f32<T>(val);
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int dm = (v >> 2) * 8 + (v & 3);
+      if (mrow + dm >= p.M) continue;
+      float val = acc[v];
+      if (p.flags & kGemmRelu) val = fmaxf(val, 0.f);
+      const size_t off = row0 + dm * ld;
+      if (p.out_kind == 1) reinterpret_cast<float*>(obase)[off] = val;
+      else reinterpret_cast<T*>(obase)[off] = from_f32<T>(val);
     }
   }
   if (p.bump && tile_x == 0 && tile_y == 0 && tid == 0) *p.bump = *p.bump + 1;
 }
 
-template <typename T, int WM, int WN, int TM, int TN, int KW, int D, int CB = 128, bool CAND = false>
+template <typename T, int WM, int WN, int KW, int D, int CB = 128, bool CAND = false>
 static hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
-  constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
+  constexpr int BM = 32 * WM, BN = 32 * WN;
   constexpr int kRowBytes = CB + 16;
   dim3 grid((p.N + BN - 1) / BN, (p.M + BM - 1) / BM, p.ksplit);
   const size_t smem = (size_t)KW * 2 * (BM + BN) * kRowBytes;
@@ -370,7 +313,7 @@ static hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     const unsigned long long bit = 1ull << (dev & 63);
     if (!(raised.load(std::memory_order_acquire) & bit)) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<T, WM, WN, TM, TN, KW, D, CB, CAND>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<T, WM, WN, KW, D, CB, CAND>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       if (e != hipSuccess) return e;
       raised.fetch_or(bit, std::memory_order_release);
@@ -386,7 +329,7 @@ static hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
     q.xcd_rows = (int)grid.y;
     grid = dim3((grid.x + 7) / 8 * 8 * grid.y, 1, 1);
   }
-  hipLaunchKernelGGL((gemm_kernel<T, WM, WN, TM, TN, KW, D, CB, CAND>), grid, dim3(WM * WN * KW * 64), smem, stream, q);
+  hipLaunchKernelGGL((gemm_kernel<T, WM, WN, KW, D, CB, CAND>), grid, dim3(WM * WN * KW * 64), smem, stream, q);
   return hipGetLastError();
 }
 
@@ -415,16 +358,16 @@ static hipError_t launch_gemm_cand(int dtype, const GemmParams& p, bool plain, h
   const int tile = cand_pick_tile(p.M, p.N, p.K, dtype);
   if (dtype == 1) {
     if (const int v = gemm_lds_variant(p.M, p.N, p.K, 3, 1, false)) return launch_gemm_lds(p, v, 1, stream);
-    if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256, true>(p, stream);
-    if (p.K % 128 == 0) return launch_tile<bf16_t, 2, 2, 1, 1, 1, 2, 256, true>(p, stream);
-    return launch_tile<bf16_t, 2, 2, 1, 1, 1, 4, 128, true>(p, stream);
+    if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 2, 256, true>(p, stream);
+    if (p.K % 128 == 0) return launch_tile<bf16_t, 2, 2, 1, 2, 256, true>(p, stream);
+    return launch_tile<bf16_t, 2, 2, 1, 4, 128, true>(p, stream);
   }
   if (tile == 1) {
     const SplitShape sp = gemm_split_shape(p.M, p.N, p.K, 1, 1);
     if (sp.wm && !plain) return launch_gemm_split(p, sp.wm, stream);
-    return launch_tile<float, 4, 4, 1, 1, 1, 2, 128, true>(p, stream);
+    return launch_tile<float, 4, 4, 1, 2, 128, true>(p, stream);
   }
-  return launch_tile<float, 2, 2, 1, 1, 1, 4, 128, true>(p, stream);
+  return launch_tile<float, 2, 2, 1, 4, 128, true>(p, stream);
 }
 
 hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t stream) {
@@ -452,24 +395,24 @@ hipError_t launch_gemm(int dtype, const GemmParams& p, bool plain, hipStream_t s
   const int chunks = (p.K / (dtype == 1 ? 64 : 32) + p.ksplit - 1) / p.ksplit;   // in 128-byte units
   const int shape = tile == 0 ? gemm_tile_shape(p.M, p.N, p.ksplit, chunks) : 0;
   if (dtype == 1) {
-    if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 1, 1, 2, 256>(p, stream);
+    if (tile == 3) return launch_tile<bf16_t, 2, 4, 1, 2, 256>(p, stream);
     if (wide) {
-      if (shape == 2) return launch_tile<bf16_t, 1, 1, 1, 1, 4, 2, 256>(p, stream);
-      if (shape == 1) return launch_tile<bf16_t, 2, 1, 1, 1, 2, 2, 256>(p, stream);
-      return launch_tile<bf16_t, 2, 2, 1, 1, 1, 2, 256>(p, stream);
+      if (shape == 2) return launch_tile<bf16_t, 1, 1, 4, 2, 256>(p, stream);
+      if (shape == 1) return launch_tile<bf16_t, 2, 1, 2, 2, 256>(p, stream);
+      return launch_tile<bf16_t, 2, 2, 1, 2, 256>(p, stream);
     }
-    if (shape == 2) return launch_tile<bf16_t, 1, 1, 1, 1, 4, 4>(p, stream);
-    if (shape == 1) return launch_tile<bf16_t, 2, 1, 1, 1, 2, 4>(p, stream);
-    return chunks <= 3 ? launch_tile<bf16_t, 2, 2, 1, 1, 1, 2>(p, stream) : launch_tile<bf16_t, 2, 2, 1, 1, 1, 4>(p, stream);
+    if (shape == 2) return launch_tile<bf16_t, 1, 1, 4, 4>(p, stream);
+    if (shape == 1) return launch_tile<bf16_t, 2, 1, 2, 4>(p, stream);
+    return chunks <= 3 ? launch_tile<bf16_t, 2, 2, 1, 2>(p, stream) : launch_tile<bf16_t, 2, 2, 1, 4>(p, stream);
   }
-  if (tile == 1) return launch_tile<float, 4, 4, 1, 1, 1, 2>(p, stream);
+  if (tile == 1) return launch_tile<float, 4, 4, 1, 2>(p, stream);
   // the register queue is always filled D chunks deep (clamped re-reads when the k
   // range is shorter), so short ranges take the 2-deep variants
   const int kw = shape == 2 ? 4 : (shape == 1 ? 2 : 1);
   const bool shallow = (chunks + kw - 1) / kw <= 3;
-  if (shape == 2) return shallow ? launch_tile<float, 1, 1, 1, 1, 4, 2>(p, stream) : launch_tile<float, 1, 1, 1, 1, 4, 4>(p, stream);
-  if (shape == 1) return shallow ? launch_tile<float, 2, 1, 1, 1, 2, 2>(p, stream) : launch_tile<float, 2, 1, 1, 1, 2, 4>(p, stream);
-  return shallow ? launch_tile<float, 2, 2, 1, 1, 1, 2>(p, stream) : launch_tile<float, 2, 2, 1, 1, 1, 4>(p, stream);
+  if (shape == 2) return shallow ? launch_tile<float, 1, 1, 4, 2>(p, stream) : launch_tile<float, 1, 1, 4, 4>(p, stream);
+  if (shape == 1) return shallow ? launch_tile<float, 2, 1, 2, 2>(p, stream) : launch_tile<float, 2, 1, 2, 4>(p, stream);
+  return shallow ? launch_tile<float, 2, 2, 1, 2>(p, stream) : launch_tile<float, 2, 2, 1, 4>(p, stream);
 }
 
 }  // namespace san
