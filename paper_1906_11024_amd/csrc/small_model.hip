@@ -165,13 +165,13 @@ __device__ __forceinline__ void attend(const float* q, const float* K, const flo
     m = lanes_max<LANES>(m);
     float l = 0.f;
     for (int j = lane; j < n; j += LANES) {   // a lane's own entries
-      const float e = expf(p[j] - m);
+      const float e = p[j] == -INFINITY ? 0.f : expf(p[j] - m);
       p[j] = e;
       l += e;
     }
     l = group_sum<16>(l);
     if (LANES == 64) l = sum_xor32(sum_xor16(l));
-    inv = n > 0 ? 1.f / l : 0.f;
+    inv = l > 0.f ? 1.f / l : 0.f;   // no position, or none with a score above -inf: zero
     if (S)
       for (int j = lane; j < n; j += LANES) S[j] = p[j] * inv;
   } else {

@@ -422,6 +422,29 @@ def test_small_models_match_oracle(case, loop):
     ls.gpu.close()
 
 
+# Scores that overflow to -inf at every position give a zero context, as in the general attention kernels (debug = 2).
+@pytest.mark.parametrize("beam", [1, 4])
+@pytest.mark.parametrize("where", ["self", "ctx"])
+def test_small_models_zero_context_where_no_score_is_finite(where, beam):
+    cfg = _cfg(batch=2, beam=beam)
+    w = wl.make_weights(cfg, seed=7)
+    w[f"dec0.{where}.bq"] = np.full_like(w[f"dec0.{where}.bq"], 1e25)
+    w[f"dec0.{where}.bk"] = np.full_like(w[f"dec0.{where}.bk"], -1e25)
+    src, lens = wl.make_source(cfg, 7)
+    got = []
+    for debug in (0, 2):
+        gpu = hz.make_gpu(cfg, w, debug=debug)
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty(2 * beam, cfg["V"], device="cuda")
+        for word in (wl.BOS_ID, 5, 9):
+            gpu.decode_step(torch.full((2 * beam,), word, dtype=torch.int32, device="cuda"), logits)
+        assert (gpu.last_launch_count == 1) == (debug == 0)
+        got.append(logits.cpu().numpy())
+        gpu.close()
+    assert np.isfinite(got[1]).all()
+    assert hz.rel_err_rows(got[0], got[1].astype(np.float64)).max() <= F32_TOL
+
+
 # Several steps inside one launch, with and without end symbols and the graph flag, then single steps on the state they leave,
 # against the launches (debug = 2) on the same weights.  The seed's searches have no near ties: scores differ by
 # the roundings of 32-bit sums (2e-5 of sums of up to 40 log-probabilities).  (21 steps: no sentence leaves the batch; see
