@@ -446,6 +446,31 @@ __global__ __launch_bounds__(kSmThreads) void small_decode_kernel(SmallDecode P)
       for (int i = 1; i < parts; ++i) lse_merge(m, s_, stat[2 * (tid * parts + i)], stat[2 * (tid * parts + i) + 1]);
       lse[tid] = m + logf(s_);
     }
+    // The parts hold more than the row's R best words.  The others must not win a tie by their lower index where the score before
+    // swallows what sets words apart: all of it in a dead row's -inf, or -1e9.  Beside the sums above: 0.1 us a step for one or
+    // two rows (eight or four parts) and 0.4 for three or four (two parts), 0.6 to 0.9 in the merge below or with eight
+    // comparisons here for the latter too.
+    if constexpr (RB < 4) {
+      if (wid == 1 && lane < 8 * R) {
+        const int first = lane & ~7;   // a row's words
+        const float v = cand_v[lane];
+        const int id = cand_i[lane];
+        Cand c[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = Cand{cand_v[first + i], cand_i[first + i]};
+        int ahead = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ahead += better(c[i].v, c[i].i, v, id);
+        wave_sync();   // all of them have been read
+        if (ahead >= R) cand_i[lane] = kNone;
+      }
+    } else if (parts == 2 && wid == 1 && lane < 2 * R * R) {
+      // j words of its own part and, if this one of the other is, R - j of that are better
+      const int list = R == 3 ? lane / 3 : lane / 4, o = ((list ^ 1) + list + 1) * R - 1 - lane;
+      const bool out = better(cand_v[o], cand_i[o], cand_v[lane], cand_i[lane]);
+      wave_sync();   // all of them have been read
+      if (out) cand_i[lane] = kNone;
+    }
     __syncthreads();
     {
       // a finished hypothesis can only be extended by the end symbol, at cost 0; an empty slot, or a score that is no
@@ -457,12 +482,6 @@ __global__ __launch_bounds__(kSmThreads) void small_decode_kernel(SmallDecode P)
         if (P.eos >= 0 && tok[r] == P.eos) {
           lp = j == 0 ? 0.f : -INFINITY;
           id = list % parts != 0 ? kNone : j == 0 ? P.eos : (j - 1 < P.eos ? j - 1 : j);
-        } else if (parts > 1 && !(fabsf(cum[r]) < 256.f)) {
-          // The parts hold more than the row's R best words.  The others must not win a tie by their lower index where the
-          // score before swallows what sets words apart: a dead row's -inf, or -1e9 (below 256 it keeps 2^-16).
-          int ahead = 0;
-          for (int i = r * parts * R; i < (r + 1) * parts * R; ++i) ahead += better(cand_v[i], cand_i[i], cand_v[list * R + j], id);
-          if (ahead >= R) id = kNone;
         }
         const float sc = cum[r] + lp;
         return id == kNone || !(sc == sc) ? Cand{-INFINITY, kNone} : Cand{sc, r * V + id};

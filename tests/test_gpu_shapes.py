@@ -631,6 +631,37 @@ def test_small_models_take_the_best_words_of_dead_rows(beam, V, dead):
     assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][0], got[1][0])
 
 
+# The score so far leaves a word's score 2^-16 where the words' own differ by 4e-6: a row's best words are found before the
+# scores are added, in whichever waves' parts of the vocabulary they lie, as in the launches (debug = 2).
+@pytest.mark.parametrize("beam", [1, 2, 3, 4, 5])
+def test_small_models_take_the_best_words_under_large_scores(beam):
+    V, d, batch = 1004, 64, 16
+    cfg = _cfg(batch=batch, beam=beam, V=V)
+    assert rules.lib().small_model(d, cfg["F"], V, cfg["n_dec"], beam, batch)
+    w = wl.make_weights(cfg, seed=4)
+    last = f"dec{cfg['n_dec'] - 1}.ln3."
+    w[last + "g"], w[last + "b"] = np.zeros(d, np.float32), np.full(d, 0.125, np.float32)
+    w["w_out"] = np.full((V, d), 0.125, np.float32)               # logits of 1, exactly
+    best = np.array([991, 740, 519, 401, 300])[:beam]             # the parts of other waves have words of lower numbers
+    w["w_out"][best, 0] += 3.2e-5                                 # and of 1 + 4e-6
+    src, lens = wl.make_source(cfg, 4)
+    got = []
+    for debug in (0, 2):
+        gpu = hz.make_gpu(cfg, w, debug=debug)
+        gpu.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        cum = torch.full((batch, beam), -np.inf, device="cuda")
+        cum[:, 0] = -255.0 + 7.3 * torch.arange(batch, device="cuda")   # ends at -145
+        cum = cum.reshape(-1).contiguous()
+        toks, pars = torch.zeros(2, 1, batch * beam, dtype=torch.int32, device="cuda")
+        gpu.decode_n(1, torch.full((batch * beam,), wl.BOS_ID, dtype=torch.int32, device="cuda"), cum, toks, pars,
+                     torch.empty(batch * beam, V, device="cuda"))
+        assert (gpu.last_launch_count == 1) == (debug == 0)
+        got.append(toks.cpu().numpy().reshape(batch, beam))
+        gpu.close()
+    assert np.array_equal(got[0], got[1])
+    assert np.array_equal(np.sort(got[0], axis=1), np.tile(np.sort(best), (batch, 1)))
+
+
 # bf16 products with their operands straight to LDS, every tile of them: (row counts, widths) whose products take it, rows and
 # columns that do not fill the last tile, q/k/v segments, fp32 partials split or not, ragged encoders, candidates, vocabularies
 # that end inside a tile.  Checked: a few sentences (a product's rows do not depend on each other), the last ones among them.
